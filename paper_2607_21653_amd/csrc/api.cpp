@@ -289,7 +289,7 @@ MoeWs carve_moe(molt::Carver& c, int T, int d, int E, int K, int F, molt_dtype a
     m.hq = c.take<uint8_t>(R * F);
     m.hs = c.take<float>(R);
   }
-  m.xt = c.take<uint8_t>(R * d * dt_size(w));
+  m.xt = c.take<uint8_t>(w == MOLT_F32 ? 0 : R * d * dt_size(w));
   m.h = c.take<uint8_t>(R * F * dt_size(act));
   m.o = c.take<float>(P * d);
   m.part_elems = gemm_part_elems(T, E, d, act);
@@ -343,13 +343,15 @@ hipError_t run_moe(const MoeWs& m, const void* x, const uint8_t* xq, const float
   // for fp8 experts): gate_up reads them through the permutation, no gathered copy
   const bool rows = x_rows != nullptr &&
                     (wdt == MOLT_BF16 ? act == MOLT_BF16 : wdt == MOLT_FP8_E4M3 && xq_given);
+  // (f32 experts read the tiled token rows themselves through the permutation)
   const void* src = fp8 ? static_cast<const void*>(xq) : x;
-  if (!rows && (e = molt::launch_gather_tiled(src, m.pperm, K, m.n_padded, m.max_rows,
+  const bool gathered = !rows && wdt != MOLT_F32;
+  if (gathered && (e = molt::launch_gather_tiled(src, m.pperm, K, m.n_padded, m.max_rows,
                                               long(d) * dt_size(wdt), m.xt, s)) != hipSuccess)
     return e;
   {
     ProfScope ps(MOLT_PROF_EXPERT_GEMM, s);
-    if ((e = molt::launch_moe_gate_up(m.xt, rows ? x_rows : nullptr, xs, m.pperm, K, w_gu, s_gu, d,
+    if ((e = molt::launch_moe_gate_up(gathered ? m.xt : src, rows ? x_rows : nullptr, xs, m.pperm, K, w_gu, s_gu, d,
                                       F, wdt, m.tiles, m.n_tiles, m.max_tiles, m.tile_m, m.h,
                                       s)) != hipSuccess)
       return e;

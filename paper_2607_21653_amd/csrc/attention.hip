@@ -455,55 +455,93 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnParams p) {
 }
 
 // ---------------------------------------------------------------- f32 VALU path
-// One wavefront per (token, query head); 64 keys per step, one key per lane for the
-// scores, one dim per lane for the output. Writes per-split partials like the MFMA path.
-__global__ __launch_bounds__(kWave) void attn_f32_kernel(const float* __restrict__ q,
-                                                         const float* __restrict__ kc,
-                                                         const float* __restrict__ vc,
-                                                         AttnParams p, int D) {
+// Workgroup = (token, query head), kF32AttnWaves wavefronts that take 64-key chunks w, w + 4,
+// ... with their own running softmax, merged through LDS in wavefront order at the end. Scores:
+// one key per lane, its D-vector in 16-byte loads against q from LDS; output: one dim per lane
+// (D / 64 of them), the 16 values of a KV block contiguous, weighted by the chunk's
+// probabilities from LDS. Latency-bound at the contexts of the f32 model: a single wavefront
+// walking the keys one by one took 40 us at contexts of 64..128, this kernel 6.6 us.
+constexpr int kF32AttnWaves = 4;
+
+template <int D>
+__global__ __launch_bounds__(kF32AttnWaves * kWave) void attn_f32_kernel(
+    const float* __restrict__ q, const float* __restrict__ kc, const float* __restrict__ vc,
+    AttnParams p) {
+  constexpr int DL = D / kWave;                      // dims per lane
+  __shared__ __attribute__((aligned(16))) float s_q[D];
+  __shared__ __attribute__((aligned(16))) float s_p[kF32AttnWaves][kWave];
+  __shared__ float s_o[kF32AttnWaves][D];
+  __shared__ float s_m[kF32AttnWaves], s_l[kF32AttnWaves];
   const int t = blockIdx.x / p.Hq, hq = blockIdx.x % p.Hq;
   const int kp1 = p.k + 1;
   const int b = t / kp1, j = t % kp1;
   const int G = p.Hq / p.Hkv, h = hq / G;
   const int lim = p.ctx[b] + j;   // last visible key
-  const float* qr = q + (long(t) * p.Hq + hq) * D;
   const int* btab = p.bt + long(b) * p.max_blocks;
   const long bs = long(p.Hkv) * 16 * D;
-  const int lane = threadIdx.x;
-  float m = -INFINITY, l = 0.f;
-  float acc[4] = {0.f, 0.f, 0.f, 0.f};   // dims lane, lane+64, ... (D <= 256)
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
+  if (threadIdx.x < D) s_q[threadIdx.x] = q[(long(t) * p.Hq + hq) * D + threadIdx.x];
+  __syncthreads();
+  float m = kNegBig, l = 0.f;
+  float acc[DL];
+#pragma unroll
+  for (int c = 0; c < DL; ++c) acc[c] = 0.f;
   const float scale = 1.0f / sqrtf(float(D));
-  for (int k0 = 0; k0 <= lim; k0 += kWave) {
+  for (int k0 = kWave * wave; k0 <= lim; k0 += kWave * kF32AttnWaves) {
     const int kp = k0 + lane;
     float s = -INFINITY;
     if (kp <= lim) {
-      const float* kr = kc + btab[kp / 16] * bs + long(h) * 16 * D + (kp % 16) * D;
-      float d = 0.f;
-      for (int i = 0; i < D; ++i) d += qr[i] * kr[i];
-      s = d * scale;
+      const floatx4_t* kr = reinterpret_cast<const floatx4_t*>(kc + btab[kp / 16] * bs + long(h) * 16 * D + (kp % 16) * D);
+      floatx4_t d = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < D / 4; ++i) {
+        const floatx4_t kv = kr[i], qv = *reinterpret_cast<const floatx4_t*>(s_q + 4 * i);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) d[e] += qv[e] * kv[e];
+      }
+      s = ((d[0] + d[1]) + (d[2] + d[3])) * scale;
     }
-    const float mx = wave_max(s);
-    const float mn = fmaxf(m, mx);
-    const float alpha = m == -INFINITY ? 0.f : expf(m - mn);
+    const float mn = fmaxf(m, wave_max(s));          // finite: the chunk's first key is visible
+    const float alpha = expf(m - mn);
     const float pe = s == -INFINITY ? 0.f : expf(s - mn);
     l = l * alpha + wave_sum(pe);
-    for (int c = 0; c < 4; ++c) acc[c] *= alpha;
-    const int nk = min(kWave, lim + 1 - k0);
-    for (int key = 0; key < nk; ++key) {
-      const float pk = __shfl(pe, key, kWave);
-      const int kk = k0 + key;
-      const float* vr = vc + btab[kk / 16] * bs + long(h) * D * 16 + (kk % 16);
-      for (int c = 0; c < 4; ++c) {
-        const int dd = lane + kWave * c;
-        if (dd < D) acc[c] += pk * vr[dd * 16];
-      }
-    }
     m = mn;
+#pragma unroll
+    for (int c = 0; c < DL; ++c) acc[c] *= alpha;
+    s_p[wave][lane] = pe;                            // read by this wavefront only
+#pragma unroll
+    for (int blk = 0; blk < 4; ++blk) {
+      const int kb = k0 + 16 * blk;
+      if (kb > lim) break;
+      const float* vr = vc + btab[kb / 16] * bs + long(h) * D * 16 + lane * 16;
+#pragma unroll
+      for (int c = 0; c < DL; ++c)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const floatx4_t v = *reinterpret_cast<const floatx4_t*>(vr + c * kWave * 16 + 4 * u);
+          const floatx4_t pv = *reinterpret_cast<const floatx4_t*>(&s_p[wave][16 * blk + 4 * u]);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)                // slots past the last key hold anything
+            acc[c] += kb + 4 * u + e <= lim ? pv[e] * v[e] : 0.f;
+        }
+    }
   }
-  float* out = reinterpret_cast<float*>(p.out);
-  for (int c = 0; c < 4; ++c) {
-    const int dd = lane + kWave * c;
-    if (dd < D) out[out_index(p, t, long(hq) * D + dd, long(p.Hq) * D, 4)] = acc[c] / l;
+#pragma unroll
+  for (int c = 0; c < DL; ++c) s_o[wave][lane + kWave * c] = acc[c];
+  if (lane == 0) { s_m[wave] = m; s_l[wave] = l; }
+  __syncthreads();
+  if (threadIdx.x < D) {
+    float mm = s_m[0];
+#pragma unroll
+    for (int w = 1; w < kF32AttnWaves; ++w) mm = fmaxf(mm, s_m[w]);
+    float lt = 0.f, o = 0.f;
+#pragma unroll
+    for (int w = 0; w < kF32AttnWaves; ++w) {
+      const float f = expf(s_m[w] - mm);             // wavefronts without keys: exactly 0 * 0
+      lt += s_l[w] * f;
+      o += s_o[w][threadIdx.x] * f;
+    }
+    reinterpret_cast<float*>(p.out)[out_index(p, t, long(hq) * D + threadIdx.x, long(p.Hq) * D, 4)] = o / lt;
   }
 }
 
@@ -571,9 +609,12 @@ hipError_t launch_paged_attention(const void* q, const void* kc, const void* vc,
   p.scale_log2 = kLog2e / sqrtf(float(D));
   const int R = (Hq / Hkv) * (k + 1);
   if (dt == MOLT_F32) {
-    attn_f32_kernel<<<B * (k + 1) * Hq, kWave, 0, s>>>(static_cast<const float*>(q),
-                                                        static_cast<const float*>(kc),
-                                                        static_cast<const float*>(vc), p, D);
+    const float *qf = static_cast<const float*>(q), *kf = static_cast<const float*>(kc),
+                *vf = static_cast<const float*>(vc);
+    const int grid = B * (k + 1) * Hq, threads = kF32AttnWaves * kWave;
+    if (D == 128) attn_f32_kernel<128><<<grid, threads, 0, s>>>(qf, kf, vf, p);
+    else if (D == 64) attn_f32_kernel<64><<<grid, threads, 0, s>>>(qf, kf, vf, p);
+    else return hipErrorInvalidValue;
     return hipGetLastError();
   }
   qtile_plan(Hq / Hkv, k + 1, p.qtiles, p.tq);

@@ -9,7 +9,7 @@
 // a device-side tile table (expert, first row, end row) in padded expert order built by
 // the permutation kernel, so the host never reads expert counts.
 //
-// The f32 model (tiny test model) takes a plain VALU path over the same layouts.
+// The f32 model takes an f32 MFMA kernel over the same layouts.
 #include "device_common.h"
 #include "internal.h"
 
@@ -937,49 +937,96 @@ __global__ __launch_bounds__(kThreads) void gather_tiled_kernel(
       *reinterpret_cast<const int4*>(src + tiled_offset(pair / ktop, j, RB));
 }
 
-// ---------------------------------------------------------------- f32 VALU path
-// One workgroup per (row tile of 16, column tile of 64); each thread owns 4 outputs.
-// Operands tiled as in the MFMA path (f32 element k of row n at byte 4k).
+// ---------------------------------------------------------------- f32 MFMA path
+// The f32 model on v_mfma_f32_32x32x2_f32 (f32 products, f32 accumulation). Workgroup = one
+// 32 x 32 output tile (gate_up: its gate and its up tile), 8 wavefronts that split the K
+// slices (wavefront w takes slices w, w + 8, ...) and add their partial tiles through LDS in
+// wavefront order (deterministic). The f32 decoder's calls have a few rows, so a launch is
+// bound by its longest chain of loads and not by flops: with K = 256..512 every wavefront has
+// at most two slices, their loads all in flight at once. A lane's 16-byte load of the tiled
+// layout holds 4 consecutive k of its row, both operands alike, so element i of the 4 is the
+// operand of one MFMA (k pair (4c + i, 16 + 4c + i) of the slice). gate_up reads the token
+// rows through the permutation. One thread per output walking K element by element (the
+// kernel before) took ~154 us per launch at K = 256..512 against 3-7 us (recompute of 16
+// rows through 2 layers of the tiny decoder: 1755 -> 105 us, the attention kernel's share
+// included).
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+constexpr int kF32Waves = 8;
+
 template <int MODE>
-__global__ __launch_bounds__(kThreads) void f32_gemm_kernel(GemmParams p) {
-  const int id = blockIdx.x;
-  const int mt = id % p.n_mtiles, nt = id / p.n_mtiles;
-  int expert = 0, row0, row1;
-  if (MODE == kDense) {
-    row0 = mt * 16;
-    row1 = min(row0 + 16, p.M);
-  } else {
+__global__ __launch_bounds__(kF32Waves * kWave) void f32_gemm_kernel(GemmParams p) {
+  constexpr int NB = MODE == kGateUp ? 2 : 1;
+  __shared__ float red[kF32Waves][NB][1024];
+  const int mt = blockIdx.x % p.n_mtiles, nt = blockIdx.x / p.n_mtiles;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
+  int expert = 0, row0 = mt * 32, row1 = min(row0 + 32, p.M);
+  if (MODE != kDense) {
     const int4 t = p.tiles[mt];
     if (t.x < 0) return;
     expert = t.x;
-    row0 = t.y;
+    row0 = t.y;                       // a multiple of 32: tiles are 32 rows of one expert
     row1 = t.z;
   }
-  const int K = p.K;
-  const float* A = static_cast<const float*>(p.A);
-  const float* B = static_cast<const float*>(p.B);
-  for (int o = threadIdx.x; o < 16 * 64; o += kThreads) {
-    const int r = o / 64, c = o % 64;
-    const int grow = row0 + r;
-    const int col = nt * 64 + c;
+  const long RB = 4L * p.K;
+  const int nk = p.K / 32;
+  // the lane's row of A: its own row of the tile, or that pair's token row (rows past the end
+  // and padding rows read token 0; their outputs are not stored)
+  long arow = row0 + lane % 32;
+  if (MODE == kGateUp) {
+    const int pr = arow < row1 ? p.perm[arow] : -1;
+    arow = pr < 0 ? 0 : pr / p.ktop;
+  }
+  const uint8_t* a = static_cast<const uint8_t*>(p.A) + tiled_offset(arow, 64 * (lane / 32), RB);
+  const long brow = long(expert) * (MODE == kGateUp ? 2L * p.N : MODE == kDown ? long(p.N) : 0L) + 32L * nt;
+  const uint8_t* b[NB];
+#pragma unroll
+  for (int j = 0; j < NB; ++j) b[j] = static_cast<const uint8_t*>(p.B) + (brow + long(j) * p.N) * RB + lane * 16;
+  floatx16_t acc[NB];
+#pragma unroll
+  for (int j = 0; j < NB; ++j)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[j][e] = 0.f;
+#pragma unroll 2
+  for (int kb = wave; kb < nk; kb += kF32Waves) {
+    f32x4 av[4], bv[NB][4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      av[c] = *reinterpret_cast<const f32x4*>(a + kb * 4096L + c * 1024);
+#pragma unroll
+      for (int j = 0; j < NB; ++j) bv[j][c] = *reinterpret_cast<const f32x4*>(b[j] + kb * 4096L + c * 1024);
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[c][i], bv[j][c][i], acc[j], 0, 0, 0);
+  }
+#pragma unroll
+  for (int j = 0; j < NB; ++j)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) red[wave][j][e * kWave + lane] = acc[j][e];
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < 1024 / (kF32Waves * kWave); ++u) {
+    const int i = int(threadIdx.x) + kF32Waves * kWave * u;
+    float v[NB];
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      v[j] = red[0][j][i];
+#pragma unroll
+      for (int w = 1; w < kF32Waves; ++w) v[j] += red[w][j][i];
+    }
+    // element e of lane l: row 8 (e / 4) + 4 (l / 32) + e % 4, column l % 32
+    const int e = i / kWave, l = i % kWave;
+    const int grow = row0 + 8 * (e / 4) + 4 * (l / 32) + (e % 4), col = 32 * nt + l % 32;
     if (grow >= row1 || col >= p.N) continue;
-    auto a = [&](int kk) { return A[tiled_index(grow, kk, K, 4)]; };
+    float* C = static_cast<float*>(p.C);
     if (MODE == kGateUp) {
-      const long ng = long(expert) * 2 * p.N + col, nu = ng + p.N;
-      float g = 0.f, u = 0.f;
-      for (int kk = 0; kk < K; ++kk) {
-        g += a(kk) * B[tiled_index(ng, kk, K, 4)];
-        u += a(kk) * B[tiled_index(nu, kk, K, 4)];
-      }
-      static_cast<float*>(p.C)[tiled_index(grow, col, p.N, 4)] = silu(g) * u;
+      C[tiled_index(grow, col, p.N, 4)] = silu(v[0]) * v[NB - 1];
     } else {
-      const long n = (MODE == kDown ? long(expert) * p.N : 0) + col;
-      float s = 0.f;
-      for (int kk = 0; kk < K; ++kk) s += a(kk) * B[tiled_index(n, kk, K, 4)];
-      const long crow = MODE == kDown ? long(p.perm[grow]) : long(grow);
-      float* dst = static_cast<float*>(p.C) + crow * p.ldc + col;
-      if (MODE == kDense && p.accumulate) s += *dst;
-      *dst = s;
+      float* dst = C + (MODE == kDown ? long(p.perm[grow]) : long(grow)) * p.ldc + col;
+      *dst = MODE == kDense && p.accumulate ? *dst + v[0] : v[0];
     }
   }
 }
@@ -989,7 +1036,7 @@ __global__ __launch_bounds__(kThreads) void f32_gemm_kernel(GemmParams p) {
 // Row-tile height of the grouped expert GEMMs: large enough that an expert of average load
 // fits one tile (its weights are then streamed once), as small as that allows.
 int moe_tile_m(molt_dtype wdt, int T, int K, int E) {
-  if (wdt == MOLT_F32) return 16;
+  if (wdt == MOLT_F32) return 32;
   const long avg = (long(T) * K + E - 1) / E;
   return avg <= 24 ? 32 : avg <= 56 ? 64 : 128;
 }
@@ -1016,9 +1063,9 @@ hipError_t launch_gemm(const void* A, const void* Bw, float* C, int M, int N, in
   p.A = A; p.B = Bw; p.C = C; p.M = M; p.N = N; p.K = K; p.ldc = N;
   p.accumulate = accumulate;
   if (dt == MOLT_F32) {
-    p.n_mtiles = (M + 15) / 16;
-    p.n_ntiles = (N + 63) / 64;
-    f32_gemm_kernel<kDense><<<p.n_mtiles * p.n_ntiles, kThreads, 0, s>>>(p);
+    p.n_mtiles = (M + 31) / 32;
+    p.n_ntiles = (N + 31) / 32;
+    f32_gemm_kernel<kDense><<<p.n_mtiles * p.n_ntiles, kF32Waves * kWave, 0, s>>>(p);
     return hipGetLastError();
   }
   if (dt == MOLT_BF16 && !accumulate && M <= 128 && N >= 8192 && N % kBN == 0) {
@@ -1090,8 +1137,8 @@ hipError_t launch_moe_gate_up(const void* a, const void* a_rows, const float* a_
   p.perm = pperm; p.ktop = K_top;
   p.a_scale = a_scale; p.b_scale = s_gu; p.b_scale_ld = 2 * F;
   if (wdt == MOLT_F32) {
-    p.n_ntiles = (F + 63) / 64;
-    f32_gemm_kernel<kGateUp><<<max_tiles * p.n_ntiles, kThreads, 0, s>>>(p);
+    p.n_ntiles = F / 32;
+    f32_gemm_kernel<kGateUp><<<max_tiles * p.n_ntiles, kF32Waves * kWave, 0, s>>>(p);
     return hipGetLastError();
   }
   p.n_ntiles = F / (kBN / 2);
@@ -1112,8 +1159,8 @@ hipError_t launch_moe_down(const void* a, const float* a_scale, const int32_t* p
   p.perm = pperm;
   p.a_scale = a_scale; p.b_scale = s_d; p.b_scale_ld = d;
   if (wdt == MOLT_F32) {
-    p.n_ntiles = (d + 63) / 64;
-    f32_gemm_kernel<kDown><<<max_tiles * p.n_ntiles, kThreads, 0, s>>>(p);
+    p.n_ntiles = d / 32;
+    f32_gemm_kernel<kDown><<<max_tiles * p.n_ntiles, kF32Waves * kWave, 0, s>>>(p);
     return hipGetLastError();
   }
   p.n_ntiles = d / kBN;

@@ -130,8 +130,8 @@ hipError_t launch_qkv_rope(const void* A, const void* Bw, int M, int K_in, int H
                            const void* table, const int32_t* kv_slot, void* q_out, void* k_cache,
                            void* v_cache, hipStream_t s);
 // Grouped expert GEMMs over the tile table built by launch_route. bf16/fp8: A and the
-// weights in the tiled layout, gate_up writes h tiled; f32: row-major A and h, tiled
-// weights. Rows are padded-order; down writes o[pair]. gate_up with a_rows (the token
+// weights in the tiled layout, gate_up writes h tiled; f32: the same, gate_up's a is the
+// tiled token rows, read through pperm. Rows are padded-order; down writes o[pair]. gate_up with a_rows (the token
 // rows in the expert dtype, row-major [T, K]) reads each padded row's token row through
 // pperm instead of the gathered copy a.
 hipError_t launch_moe_gate_up(const void* a, const void* a_rows, const float* a_scale,
