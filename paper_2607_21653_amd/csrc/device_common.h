@@ -27,6 +27,12 @@ MOLT_DEV uint16_t f32_to_bf16(float f) {
   return uint16_t(u >> 16);
 }
 
+// two at once on the hardware conversion (v_cvt_pk_bf16_f32: the same rounding): a in the low half
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+MOLT_DEV uint32_t f32x2_to_bf16(float a, float b) {
+  return __builtin_bit_cast(uint32_t, bf16x2_t{__bf16(a), __bf16(b)});
+}
+
 MOLT_DEV float round_to_bf16(float f) { return bf16_to_f32(f32_to_bf16(f)); }
 
 // ---------------------------------------------------------------- fp8 e4m3fn (OCP)

@@ -717,33 +717,34 @@ __global__ __launch_bounds__(128 * WN) void lds_gemm_kernel(GemmParams p, float*
   }
 }
 
-// ---------------------------------------------------------------- big-tile dense GEMM
-// The LM head (640 x 151936 x 2048) is bound by what the memory pipeline can hand the
-// MFMAs, so its tile is sized for flops per loaded byte: 160 rows x 256 columns per
-// workgroup, 101 flops per byte (the 128 x 128 LDS-tiled kernel reaches 64). Wavefront w
-// computes all 160 rows x columns 64 w .. 64 w + 63, so the activation tile is shared by the
-// four wavefronts and each weight column block belongs to one of them:
-// * the 5 activation blocks (tiled, 4 KB per K slice) go through a 4-stage LDS ring, copied
+// ---------------------------------------------------------------- big-tile GEMM
+// GEMMs with many rows and columns are bound by what the memory pipeline can hand the MFMAs,
+// so their tile is sized for flops per loaded byte: 32 AB rows x 256 columns per workgroup
+// (AB = 5: 101 flops per byte, where the 128 x 128 LDS-tiled kernel reaches 64). Wavefront w
+// computes all rows of 64 columns, so the activation tile is shared by the four wavefronts
+// and each weight column block belongs to one of them:
+// * the AB activation blocks (tiled, 4 KB per K slice) go through a 4-stage LDS ring, copied
 //   by the LDS-DMA form of the buffer load three slices ahead (each wavefront a quarter of
 //   every block; it waits for its own copies and one barrier per slice publishes them);
 // * the wavefront's 2 weight blocks are loaded straight into MFMA operand registers (the
-//   tiled layout is the fragment layout) kBigDepth slices ahead: they never touch LDS.
-// Per 16-wide k step 5 LDS fragments and 2 register fragments feed 10 MFMAs. The barrier
+//   tiled layout is the fragment layout) DEPTH slices ahead: they never touch LDS.
+// Per 16-wide k step AB LDS fragments and 2 register fragments feed 2 AB MFMAs. The barrier
 // sits before the last k step of a slice, so the next slice's first fragments are read
-// behind that step's MFMAs. The row tiles of one column tile are consecutive on one XCD, so
-// its weights come from HBM once.
-constexpr int kBigBM = 160, kBigBN = 256;
-constexpr int kBigAB = kBigBM / 32;            // activation blocks per K slice
+// behind that step's MFMAs. Loads past the last slice go through a resource of size 0: they
+// move no data. The row tiles of one column tile are consecutive on one XCD, so its weights
+// come from HBM once. Up to 4 blocks fit two workgroups on a CU (256 registers a wavefront,
+// at 4 blocks with 2 weight slices in flight): one's loads and stores overlap the other's
+// MFMAs, which made 128-row tiles the best per row (LM head, 640 x 151936 x 2048: 160 rows one
+// a CU 401 us, 128 rows two a CU 360 us, one a CU 408 us; 192 rows 476 us).
+constexpr int kBigBN = 256;
 constexpr int kBigAStages = 4;
-constexpr int kBigAStage = kBigAB * 4096;
-constexpr int kBigDepth = 3;                   // weight slices in flight per wavefront
 constexpr int kBigBLoads = 8;                  // weight loads per wavefront per slice
 
 // Buffer resource word 3 for raw byte-addressed loads (32-bit data format, no swizzle).
 constexpr int kRawRsrcWord3 = 0x00020000;
 
-MOLT_DEV __amdgpu_buffer_rsrc_t raw_rsrc(const void* base, long bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, int(bytes), kRawRsrcWord3);
+MOLT_DEV __amdgpu_buffer_rsrc_t raw_rsrc(const void* base, int bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, kRawRsrcWord3);
 }
 
 // Each lane copies the 16 bytes at voff + soff of the buffer into LDS at l + 16 * lane
@@ -753,85 +754,69 @@ MOLT_DEV void lds_dma16(__amdgpu_buffer_rsrc_t r, int voff, int soff, uint8_t* l
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)l, 16, voff, soff, 0, 0);
 }
 
-__global__ __launch_bounds__(kThreads) void bigtile_gemm_kernel(GemmParams p) {
-  __shared__ __attribute__((aligned(16))) uint8_t ring[kBigAStages * kBigAStage];
-  const int total = p.n_mtiles * p.n_ntiles;
-  const int chunk = (total + 7) / 8;
-  const int k8 = blockIdx.x / 8;
-  const int id = (blockIdx.x % 8) * chunk + k8;
-  if (k8 >= chunk || id >= total) return;
-  const int mt = id % p.n_mtiles, nt = id / p.n_mtiles;
-  const int row0 = mt * kBigBM, n0 = nt * kBigBN;
-  const long RB = long(p.K) * 2;
-  const int nk = int(RB / kRowBytes);
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const int lane = threadIdx.x % kWave;
-  const int last_a = (p.M - 1) & ~31, last_b = (p.N - 1) & ~31;
-  // byte offsets relative to the activation matrix and to this tile's first weight row; row
-  // blocks past the end re-read the last one (their results are never stored)
-  const __amdgpu_buffer_rsrc_t ra = raw_rsrc(p.A, long(last_a + 32) * RB);
-  const __amdgpu_buffer_rsrc_t rb = raw_rsrc(static_cast<const uint8_t*>(p.B) + long(n0) * RB,
-                                             long(min(n0 + kBigBN, last_b + 32) - n0) * RB);
-  int avoff[kBigAB], bvoff[2];
-#pragma unroll
-  for (int j = 0; j < kBigAB; ++j) avoff[j] = int(min(row0 + 32 * j, last_a) * RB) + wave * 1024 + lane * 16;
-#pragma unroll
-  for (int j = 0; j < 2; ++j) bvoff[j] = int((min(n0 + 64 * wave + 32 * j, last_b) - n0) * RB) + lane * 16;
-  // slices past the end re-copy the last one
+// acc[i][j] = rows 32 i .. of the activation tile x the wavefront's column block j over nk K
+// slices. abase / avoff: each lane's source of its 16 bytes of every block's copy (wavefront w
+// copies quarter w); bbase / bvoff: the lane's bytes of its weight blocks. On return no copy is
+// in flight; other wavefronts may still read the ring.
+template <int AB, int DEPTH>
+MOLT_DEV void bigtile_loop(floatx16_t (&acc)[AB][2], uint8_t* ring, const void* abase, int abytes,
+                           const int (&avoff)[AB], const void* bbase, int bbytes,
+                           const int (&bvoff)[2], int nk, int wave, int lane) {
+  constexpr int kStage = AB * 4096;
   auto issue_a = [&](int kb) __attribute__((always_inline)) {
-    const int soff = min(kb, nk - 1) * 4096;
-    uint8_t* dst = ring + (kb % kBigAStages) * kBigAStage + wave * 1024;
+    const __amdgpu_buffer_rsrc_t ra = raw_rsrc(abase, kb < nk ? abytes : 0);
+    uint8_t* dst = ring + (kb % kBigAStages) * kStage + wave * 1024;
 #pragma unroll
-    for (int j = 0; j < kBigAB; ++j) lds_dma16(ra, avoff[j], soff, dst + j * 4096);
+    for (int j = 0; j < AB; ++j) lds_dma16(ra, avoff[j], kb * 4096, dst + j * 4096);
   };
   typedef bf16x8_t BSlice[4][2];   // [k step][column block]
   auto load_b = [&](int kb, BSlice& b) __attribute__((always_inline)) {
-    const int soff = min(kb, nk - 1) * 4096;
+    const __amdgpu_buffer_rsrc_t rb = raw_rsrc(bbase, kb < nk ? bbytes : 0);
 #pragma unroll
     for (int c = 0; c < 4; ++c)
 #pragma unroll
       for (int j = 0; j < 2; ++j)
-        b[c][j] = __builtin_bit_cast(bf16x8_t, __builtin_amdgcn_raw_buffer_load_b128(rb, bvoff[j] + c * 1024, soff, 0));
+        b[c][j] = __builtin_bit_cast(bf16x8_t, __builtin_amdgcn_raw_buffer_load_b128(rb, bvoff[j] + c * 1024, kb * 4096, 0));
   };
-  floatx16_t acc[kBigAB][2];
 #pragma unroll
-  for (int i = 0; i < kBigAB; ++i)
+  for (int i = 0; i < AB; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
   // activation fragments of one k step, two register sets
-  bf16x8_t af[2][kBigAB];
+  bf16x8_t af[2][AB];
   auto frag = [&](const uint8_t* base, int c, int set) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < kBigAB; ++i) af[set][i] = *reinterpret_cast<const bf16x8_t*>(base + i * 4096 + c * 1024);
+    for (int i = 0; i < AB; ++i) af[set][i] = *reinterpret_cast<const bf16x8_t*>(base + i * 4096 + c * 1024);
   };
   auto step = [&](int set, const bf16x8_t (&b)[2]) __attribute__((always_inline)) {
     // the scheduler would otherwise sink the next step's reads below these MFMAs
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int i = 0; i < kBigAB; ++i)
+    for (int i = 0; i < AB; ++i)
 #pragma unroll
       for (int j = 0; j < 2; ++j) acc[i][j] = mfma(af[set][i], b[j], acc[i][j]);
     __builtin_amdgcn_sched_barrier(0);
   };
-  BSlice bs[kBigDepth];
+  BSlice bs[DEPTH];
   issue_a(0);
   issue_a(1);
   issue_a(2);
 #pragma unroll
-  for (int J = 0; J < kBigDepth; ++J) load_b(J, bs[J]);
+  for (int J = 0; J < DEPTH; ++J) load_b(J, bs[J]);
   // slice 0's activations are in (what follows them in the queue may be in flight)
-  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * kBigAB + kBigBLoads * kBigDepth) : "memory");
+  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * AB + kBigBLoads * DEPTH) : "memory");
   frag(ring + lane * 16, 0, 0);
   // Per slice kb the vector-memory queue gets: activations kb + 3 (after the barrier), then
   // weights kb + depth (after the last MFMAs). The barrier of slice kb needs activations
   // kb + 1, issued in slice kb - 2; what may still be in flight behind them is at least
   // weights kb - 2 + depth, activations kb + 2 and weights kb - 1 + depth (exactly that from
   // slice 2 on, more before), so waiting for that many leaves it complete.
-  constexpr int kAWait = 2 * kBigBLoads + kBigAB;
+  static_assert(DEPTH >= 2, "the first barriers count two weight slices behind the copies");
+  constexpr int kAWait = 2 * kBigBLoads + AB;
   auto body = [&](int kb, BSlice& b) __attribute__((always_inline)) {
-    const uint8_t* base = ring + (kb % kBigAStages) * kBigAStage + lane * 16;
+    const uint8_t* base = ring + (kb % kBigAStages) * kStage + lane * 16;
     frag(base, 1, 1);
     step(0, b[0]);
     frag(base, 2, 0);
@@ -843,42 +828,150 @@ __global__ __launch_bounds__(kThreads) void bigtile_gemm_kernel(GemmParams p) {
     // stage takes slice kb + 3
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(kAWait) : "memory");
     issue_a(kb + 3);
-    frag(ring + ((kb + 1) % kBigAStages) * kBigAStage + lane * 16, 0, 0);
+    frag(ring + ((kb + 1) % kBigAStages) * kStage + lane * 16, 0, 0);
     step(1, b[3]);
-    load_b(kb + kBigDepth, b);
+    load_b(kb + DEPTH, b);
   };
   int kb = 0;
-  for (; kb + kBigDepth - 1 < nk; kb += kBigDepth) {   // register sets are indexed statically
+  for (; kb + DEPTH - 1 < nk; kb += DEPTH) {   // register sets are indexed statically
 #pragma unroll
-    for (int J = 0; J < kBigDepth; ++J) body(kb + J, bs[J]);
+    for (int J = 0; J < DEPTH; ++J) body(kb + J, bs[J]);
   }
 #pragma unroll
-  for (int J = 0; J < kBigDepth - 1; ++J)
+  for (int J = 0; J < DEPTH - 1; ++J)
     if (kb + J < nk) body(kb + J, bs[J]);
-  // no copy may still be writing into LDS when the workgroup ends
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  // acc[i][j][e]: row 32 i + 8 (e / 4) + 4 lgrp + e % 4, column 64 wave + 32 j + lcol
+}
+
+// Dense big-tile GEMM. Wavefront w takes column blocks 128 (w / 2) + 32 (w % 2) + {0, 64} of the
+// tile: with ROPE a rotation pair (i, i + 64) of a head is then acc[.][0] and acc[.][1] of one
+// lane. ROPE: the tile's two heads are rotated in registers (f64, the step's table), rounded to
+// bf16 into the idle ring and written from there: q and K rows 16 bytes per store; V heads sit
+// transposed in the ring, so that the lanes of a store are consecutive tokens of one dim. (With
+// V read from rows and each token's cache slot from memory, the few V tiles alone took 40 us.)
+template <int AB, bool ROPE>
+__global__ __launch_bounds__(kThreads, AB <= 4 ? 2 : 1) void bigtile_gemm_kernel(GemmParams p, RopeKv rk) {
+  constexpr int BM = 32 * AB;
+  // one LDS object (the compiler tells the ring's copies from other reads by their object):
+  // the ring, then the cache slots of the tile's rows
+  __shared__ __attribute__((aligned(16))) uint8_t ring[kBigAStages * AB * 4096 + (ROPE ? BM * 4 : 0)];
+  const int total = p.n_mtiles * p.n_ntiles;
+  const int chunk = (total + 7) / 8;
+  const int k8 = blockIdx.x / 8;
+  const int id = (blockIdx.x % 8) * chunk + k8;
+  if (k8 >= chunk || id >= total) return;
+  const int mt = id % p.n_mtiles, nt = id / p.n_mtiles;
+  const int row0 = mt * BM, n0 = nt * kBigBN;
+  const long RB = long(p.K) * 2;
+  const int nk = int(RB / kRowBytes);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int lane = threadIdx.x % kWave;
+  const int last_a = (p.M - 1) & ~31, last_b = (p.N - 1) & ~31;
+  const int c0 = 128 * (wave >> 1) + 32 * (wave & 1);     // first column of block 0 in the tile
+  // byte offsets relative to the activation matrix and to this tile's first weight row; row
+  // blocks past the end re-read the last one (their results are never stored)
+  int avoff[AB], bvoff[2];
+#pragma unroll
+  for (int j = 0; j < AB; ++j) avoff[j] = int(min(row0 + 32 * j, last_a) * RB) + wave * 1024 + lane * 16;
+#pragma unroll
+  for (int j = 0; j < 2; ++j) bvoff[j] = int((min(n0 + c0 + 64 * j, last_b) - n0) * RB) + lane * 16;
+  floatx16_t acc[AB][2];
+  bigtile_loop<AB, AB == 4 ? 2 : 3>(acc, ring, p.A, int(long(last_a + 32) * RB), avoff,
+                      static_cast<const uint8_t*>(p.B) + long(n0) * RB,
+                      int(long(min(n0 + kBigBN, last_b + 32) - n0) * RB), bvoff, nk, wave, lane);
+  // acc[i][j][e]: row 32 i + 8 (e / 4) + 4 lgrp + e % 4, column c0 + 64 j + lcol
   const int lcol = lane % 32, lgrp = lane / 32;
+  if constexpr (ROPE) {
+    const int h = 2 * nt + (wave >> 1), nheads = rk.Hq + 2 * rk.Hkv;
+    const int pi = 32 * (wave & 1) + lcol;
+    // bf16 tile in the ring, one half per head: q and K [BM][128], V [128][BM]
+    uint16_t* ob = reinterpret_cast<uint16_t*>(ring) + (wave >> 1) * BM * 128;
+    int* s_slot = reinterpret_cast<int*>(ring + kBigAStages * AB * 4096);
+    static_assert(2 * BM * 256 <= kBigAStages * AB * 4096, "the bf16 tile fits the ring");
+    const bool rotate = h < rk.Hq + rk.Hkv;
+    lds_barrier();                                        // every wavefront is done with the ring
+    if (int(threadIdx.x) < BM) s_slot[threadIdx.x] = row0 + int(threadIdx.x) < p.M ? rk.slot[row0 + threadIdx.x] : -1;
+#pragma unroll
+    for (int i = 0; i < AB; ++i) {
+      if (rotate) {
+        double2 cs[16];
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+          cs[e] = rk.table[long(min(row0 + 32 * i + 8 * (e / 4) + 4 * lgrp + (e % 4), p.M - 1)) * 64 + pi];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const double a = acc[i][0][e], c = acc[i][1][e];
+          uint16_t* o = ob + (32 * i + 8 * (e / 4) + 4 * lgrp + (e % 4)) * 128 + pi;
+          float lo = float(a * cs[e].x - c * cs[e].y), hi = float(c * cs[e].x + a * cs[e].y);
+          // rounded to f32 first, as everywhere (the compiler would go from f64 to bf16 at once)
+          asm("" : "+v"(lo), "+v"(hi));
+          const uint32_t v = f32x2_to_bf16(lo, hi);
+          o[0] = uint16_t(v);
+          o[64] = uint16_t(v >> 16);
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {                   // 4 consecutive rows of one dim
+            *reinterpret_cast<uint2*>(ob + (pi + 64 * j) * BM + 32 * i + 8 * q + 4 * lgrp) =
+                make_uint2(f32x2_to_bf16(acc[i][j][4 * q], acc[i][j][4 * q + 1]),
+                           f32x2_to_bf16(acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]));
+          }
+      }
+    }
+    lds_barrier();
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh) {
+      const int hd = 2 * nt + hh;                         // workgroup-uniform
+      if (hd >= nheads) break;
+      const uint16_t* oh = reinterpret_cast<const uint16_t*>(ring) + hh * BM * 128;
+      if (hd < rk.Hq + rk.Hkv) {
+#pragma unroll 4
+        for (int w = threadIdx.x; w < BM * 16; w += kThreads) {
+          const int r = w / 16, ch = w % 16, t = row0 + r, sl = s_slot[r];
+          if (t >= p.M || (hd >= rk.Hq && sl < 0)) continue;
+          uint16_t* dst = hd < rk.Hq ? rk.q + (long(t) * rk.Hq + hd) * 128
+                                     : rk.kc + ((long(sl >> 4) * rk.Hkv + (hd - rk.Hq)) * 16 + (sl & 15)) * 128;
+          *reinterpret_cast<uint4*>(dst + 8 * ch) = *reinterpret_cast<const uint4*>(oh + r * 128 + 8 * ch);
+        }
+      } else {
+        const int hk = hd - rk.Hq - rk.Hkv;
+#pragma unroll 8
+        for (int w = threadIdx.x; w < BM * 128; w += kThreads) {
+          const int r = w % BM, i = w / BM, sl = s_slot[r];
+          if (sl < 0) continue;
+          rk.vc[((long(sl >> 4) * rk.Hkv + hk) * 128 + i) * 16 + (sl & 15)] = oh[w];
+        }
+      }
+    }
+    return;
+  }
   float* C = static_cast<float*>(p.C);
-  if (!p.accumulate && row0 + kBigBM <= p.M && n0 + kBigBN <= p.N) {
-    // whole tile (all but the last column tile): no bounds checks between the stores (the
-    // LM head: 451 -> 411 us; nontemporal stores measured 420 us; without any stores 370 us:
-    // the tiles of a round end together and their 40 MB of logits go out in one burst)
-    float* base = C + long(row0 + 4 * lgrp) * p.ldc + n0 + 64 * wave + lcol;
+  if (row0 + BM <= p.M && n0 + kBigBN <= p.N) {
+    // whole tile (all but the last row and column tiles): no bounds checks between the stores
+    // (the LM head: 451 -> 411 us; nontemporal stores measured 420 us), and with accumulate 16
+    // loads ahead of their stores
+    float* base = C + long(row0 + 4 * lgrp) * p.ldc + n0 + c0 + lcol;
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int i = 0; i < kBigAB; ++i)
+      for (int i = 0; i < AB; ++i) {
+        if (p.accumulate) {
 #pragma unroll
-        for (int e = 0; e < 16; ++e) base[long(32 * i + 8 * (e / 4) + (e % 4)) * p.ldc + 32 * j] = acc[i][j][e];
+          for (int e = 0; e < 16; ++e) acc[i][j][e] += base[long(32 * i + 8 * (e / 4) + (e % 4)) * p.ldc + 64 * j];
+        }
+#pragma unroll
+        for (int e = 0; e < 16; ++e) base[long(32 * i + 8 * (e / 4) + (e % 4)) * p.ldc + 64 * j] = acc[i][j][e];
+      }
     return;
   }
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
-    const int col = n0 + 64 * wave + 32 * j + lcol;
+    const int col = n0 + c0 + 64 * j + lcol;
     if (col >= p.N) continue;
 #pragma unroll
-    for (int i = 0; i < kBigAB; ++i)
+    for (int i = 0; i < AB; ++i)
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
         const int grow = row0 + 32 * i + 8 * (e / 4) + 4 * lgrp + (e % 4);
@@ -887,6 +980,26 @@ __global__ __launch_bounds__(kThreads) void bigtile_gemm_kernel(GemmParams p) {
         *dst = p.accumulate ? *dst + acc[i][j][e] : acc[i][j][e];
       }
   }
+}
+
+template <bool ROPE>
+hipError_t run_bigtile(GemmParams p, const RopeKv& rk, int ab, hipStream_t s) {
+  p.n_mtiles = (p.M + 32 * ab - 1) / (32 * ab);
+  p.n_ntiles = (p.N + kBigBN - 1) / kBigBN;
+  const int grid = (p.n_mtiles * p.n_ntiles + 7) / 8 * 8;
+  switch (ab) {
+    case 2: bigtile_gemm_kernel<2, ROPE><<<grid, kThreads, 0, s>>>(p, rk); break;
+    case 3: bigtile_gemm_kernel<3, ROPE><<<grid, kThreads, 0, s>>>(p, rk); break;
+    case 4: bigtile_gemm_kernel<4, ROPE><<<grid, kThreads, 0, s>>>(p, rk); break;
+    case 5:
+      if constexpr (!ROPE) {
+        bigtile_gemm_kernel<5, false><<<grid, kThreads, 0, s>>>(p, rk);
+        break;
+      }
+      [[fallthrough]];
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
 }
 
 // C (+)= sum over s of part[s], in split order
@@ -986,7 +1099,6 @@ __global__ __launch_bounds__(kF32Waves * kWave) void f32_gemm_kernel(GemmParams 
   for (int j = 0; j < NB; ++j)
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[j][e] = 0.f;
-#pragma unroll 2
   for (int kb = wave; kb < nk; kb += kF32Waves) {
     f32x4 av[4], bv[NB][4];
 #pragma unroll
@@ -1041,17 +1153,40 @@ int moe_tile_m(molt_dtype wdt, int T, int K, int E) {
   return avg <= 24 ? 32 : avg <= 56 ? 64 : 128;
 }
 
-// Tile height and split-K count of a dense bf16 GEMM: 128-row tiles when there are plenty
-// of them, else 64; then the K range is halved while the grid is under one workgroup per
-// CU, each split keeps >= 4 slices and the partial sums fit `part_elems` floats.
-GemmPlan gemm_plan(int M, int N, int K, long part_elems) {
-  GemmPlan g{128, 1};
+// Plan of a dense bf16 GEMM: big tiles of 32 ab rows x 256 columns (ab > 0), or the LDS-tiled
+// kernel with bm x 128 tiles and split-K. LDS-tiled: 128-row tiles when there are plenty of
+// them, else 64; then the K range is halved while the grid is under one workgroup per CU, each
+// split keeps >= 4 slices and the partial sums fit `part_elems` floats.
+// Between them the busiest CU decides: tiles per CU (rounded up) x the time of one tile, which
+// was measured per 32 slices with the chip full (us): LDS-tiled 64 rows 11.5, 128 rows 20.5;
+// big tiles of 64 rows 18, 96 rows 24, 128 rows 30, 160 rows 40; with the RoPE epilogue 13, 24
+// and 20.5, 28.5, 33, 54 (160 rows leave one workgroup a CU, with nothing to hide the epilogue
+// behind: not used). The kernels both ways (us, LDS-tiled / big): 4000 x 5120 x 2048 135 / 87
+// (160 rows), 4000 x 2048 x 4096 85 / 65 (128 rows), 2304 x 5120 x 2048 62 / 47 and 2304 x 2048
+// x 4096 64 / 42 (96 rows), 640 x 5120 x 2048 25 / 21 (64 rows); 1024 x 2048 x 4096 26 / 32 and
+// 640 x 2048 x 4096 29 / 30 stay LDS-tiled. QKV with RoPE at 4000 rows 138 / 98 (128 rows), at
+// 2304 83 / 63 (96 rows), at 640 35 / 33 (64 rows).
+GemmPlan gemm_plan(int M, int N, int K, long part_elems, bool rope) {
+  constexpr long kCus = 256;
+  GemmPlan g{128, 1, 0};
   const long nt = (N + kBN - 1) / kBN;
   if ((M + 127) / 128 * nt < 512) g.bm = 64;
   const long wg = (M + g.bm - 1) / g.bm * nt;
   const int nk = int(2L * K / kRowBytes);
-  while (wg * g.splits < 256 && nk / (2 * g.splits) >= 4 && 2L * g.splits * M * N <= part_elems)
-    g.splits *= 2;
+  long splits = 1;                       // without the limit of part_elems
+  while (!rope && wg * splits < 256 && nk / (2 * splits) >= 4) splits *= 2;
+  if (long(M + 31) * 2 * K < (1L << 31) && long(kBigBN) * 2 * K < (1L << 31)) {   // 32-bit buffer offsets
+    constexpr double kTile[2][6] = {{0, 0, 18.0, 24.0, 30.0, 40.0}, {0, 0, 20.5, 28.5, 33.0, 54.0}};
+    constexpr double kLdsTile[2][2] = {{11.5, 20.5}, {13.0, 24.0}};
+    double best = double((wg * splits + kCus - 1) / kCus) * kLdsTile[rope][g.bm / 128] / double(splits);
+    for (int ab = 2; ab <= (rope ? 4 : 5); ++ab) {
+      const long tiles = long((M + 32 * ab - 1) / (32 * ab)) * ((N + kBigBN - 1) / kBigBN);
+      const double t = double((tiles + kCus - 1) / kCus) * kTile[rope][ab];
+      if (t < best) { best = t; g.ab = ab; }
+    }
+    if (g.ab > 0) return g;
+  }
+  while (g.splits < splits && 2L * g.splits * M * N <= part_elems) g.splits *= 2;
   return g;
 }
 
@@ -1079,18 +1214,8 @@ hipError_t launch_gemm(const void* A, const void* Bw, float* C, int M, int N, in
     p.n_ntiles = N / kBN;
     return run_stream<false, kDown>(p, M <= 32 ? 32 : M <= 64 ? 64 : 128, s);
   }
-  if (M >= kBigBM && N >= 8192 && long((M + kBigBM - 1) / kBigBM) * ((N + kBigBN - 1) / kBigBN) >= 512 &&
-      long(M + 31) * 2 * K < (1L << 31) && long(kBigBN) * 2 * K < (1L << 31)) {
-    // many more columns than rows (the LM head): big tiles fed by LDS-DMA (32-bit buffer
-    // offsets: the activations and one tile's weights under 2 GB). Below 160 rows (the
-    // draft head's LM head: 128) the 128 x 128 LDS kernel measured 5% faster.
-    p.n_mtiles = (M + kBigBM - 1) / kBigBM;
-    p.n_ntiles = (N + kBigBN - 1) / kBigBN;
-    const int grid = (p.n_mtiles * p.n_ntiles + 7) / 8 * 8;
-    bigtile_gemm_kernel<<<grid, kThreads, 0, s>>>(p);
-    return hipGetLastError();
-  }
   const GemmPlan g = gemm_plan(M, N, K, part_elems);
+  if (g.ab > 0) return run_bigtile<false>(p, RopeKv{}, g.ab, s);
   p.n_mtiles = (M + g.bm - 1) / g.bm;
   p.n_ntiles = (N + kBN - 1) / kBN;
   const int grid = (p.n_mtiles * p.n_ntiles * g.splits + 7) / 8 * 8;
@@ -1114,7 +1239,8 @@ hipError_t launch_qkv_rope(const void* A, const void* Bw, int M, int K_in, int H
   p.A = A; p.B = Bw; p.M = M; p.N = (Hq + 2 * Hkv) * 128; p.K = K_in; p.ldc = p.N;
   RopeKv rk{static_cast<const double2*>(table), kv_slot, Hq, Hkv, static_cast<uint16_t*>(q_out),
             static_cast<uint16_t*>(k_cache), static_cast<uint16_t*>(v_cache)};
-  const GemmPlan g = gemm_plan(M, p.N, K_in, 0);     // no split: the epilogue needs whole sums
+  const GemmPlan g = gemm_plan(M, p.N, K_in, 0, true);   // no split: the epilogue needs whole sums
+  if (g.ab > 0) return run_bigtile<true>(p, rk, g.ab, s);
   p.n_mtiles = (M + g.bm - 1) / g.bm;
   p.n_ntiles = Hq + 2 * Hkv;
   const int grid = (p.n_mtiles * p.n_ntiles + 7) / 8 * 8;

@@ -115,11 +115,11 @@ long max_padded_rows(int T, int E, int K);
 // ------------------------------------------------------------- GEMMs
 // C[M, N] (f32, row-major) = A[M, K] * B[N, K]^T, A/B in dt (F32 or BF16), both tiled (rows
 // padded to 32); epilogue adds into C when accumulate. bf16 may split K when `part` holds
-// enough floats for the partial sums (gemm_plan). With splits_out the fixed-order sum of
+// enough floats for the partial sums (gemm_plan; never with big tiles, ab > 0). With splits_out the fixed-order sum of
 // the partials is left to the caller: *splits_out = S > 1 means C was not touched and
 // part[s * M * N ..] holds split s; S = 1 means C was written as usual.
-struct GemmPlan { int bm, splits; };
-GemmPlan gemm_plan(int M, int N, int K, long part_elems);
+struct GemmPlan { int bm, splits, ab; };
+GemmPlan gemm_plan(int M, int N, int K, long part_elems, bool rope = false);
 hipError_t launch_gemm(const void* A, const void* Bw, float* C, int M, int N, int K, molt_dtype dt,
                        bool accumulate, float* part, long part_elems, hipStream_t s,
                        int* splits_out = nullptr);
