@@ -85,6 +85,36 @@ MOLT_DEV int kswz(int key, int blk) {
 }
 MOLT_DEV int vswz(int dim) { return ((dim >> 2) ^ (dim >> 3)) & 1; }
 
+// Row r of a query tile (position j0 + r / G, query head h G + r % G): its output, or this split's
+// partials. o(dt): the lane's elements of O^T tile dt, dims 16 dt + 4 g4 + e; lt the row's sum.
+template <int D, typename O>
+MOLT_DEV void store_row(const AttnParams& p, int b, int h, int G, int r, int r0, int j0, int R, int bh,
+                        int split, int g4, O o, float m, float lt) {
+  const int j = j0 + r / G, gi = r % G;
+  if (p.splits == 1) {
+    const float inv = lt > 0.f ? 1.f / lt : 0.f;
+#pragma unroll
+    for (int dt = 0; dt < D / 16; ++dt) {
+      // the 4 consecutive columns of the lane's rows: one 8-byte store in either layout
+      const floatx4_t x = o(dt);
+      uint16_t v[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = f32_to_bf16(x[e] * inv);
+      *reinterpret_cast<uint2*>(p.out + out_index(p, long(b) * (p.k + 1) + j, (h * G + gi) * D + 16 * dt + 4 * g4,
+                                                   long(p.Hq) * D, 2)) =
+          make_uint2(uint32_t(v[0]) | (uint32_t(v[1]) << 16), uint32_t(v[2]) | (uint32_t(v[3]) << 16));
+    }
+  } else {
+    const long pr = (long(bh) * p.splits + split) * R + r0 + r;
+#pragma unroll
+    for (int dt = 0; dt < D / 16; ++dt) *reinterpret_cast<floatx4_t*>(p.part_o + pr * D + 16 * dt + 4 * g4) = o(dt);
+    if (g4 == 0) {
+      p.part_ml[pr * 2 + 0] = m;
+      p.part_ml[pr * 2 + 1] = lt;
+    }
+  }
+}
+
 template <int D, int NW, int KS>
 __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void attn_lds_kernel(AttnParams p) {
   constexpr int kThreads = 64 * NW;
@@ -380,36 +410,254 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void attn_lds_kernel(Attn
   if (!active) return;
 
   // row totals across the 4 lane groups, then the output (or this split's partials)
+  const float lt = rows_sum4(l_run[0]);
+  const int r = 16 * rtile + l16;
+  if (r >= Rt) return;
+  store_row<D>(p, b, h, G, r, r0, j0, R, bh, split, g4, [&](int dt) { return o[dt][0]; }, m_run[0], lt);
+}
+
+// ---------------------------------------------------------------- many query rows
+// Query tiles of more than 64 rows (72 rows at 8 drafts of 8 query heads, prefill windows: 128):
+// 4 wavefronts, each with one or two 16-row tiles, so that a fragment of K or V read from LDS
+// feeds two tiles' MFMAs (with one tile per wavefront, 8 wavefronts read 128 KB of LDS per
+// 32-key pair for 128 rows, 1024 cycles against 768 of MFMAs). K and V go into a 4-stage LDS
+// ring by LDS-DMA, 3 pairs ahead, without registers (wavefront w copies block w of K0, K1, V0,
+// V1; the swizzles are in the lanes' source addresses), block ids by scalar loads one pair
+// earlier, one barrier per pair, two workgroups a CU. Prefill windows run their longest query
+// tiles first. Measured (us, one-tile wavefronts before / now): prompt of 2 x 2000 positions 192 /
+// 120, 256 positions at context 8192 82 / 66, 72 rows x 256 sequences at context 2048 232 / 204
+// (ordinary instead of nontemporal copies there: 246; 5 stages or another wavefront taking the
+// fifth tile in every other workgroup: the same).
+constexpr int kRawRsrcWord3 = 0x00020000;   // raw byte-addressed buffer
+constexpr int kRowStages = 4;
+constexpr int kRowWaves = 4;
+
+// What a workgroup of attn_rows_kernel works on (all uniform).
+struct RowTile {
+  int b, h, bh, split, ctx, j0, Rt, r0, blk0, blk1, npairs;
+};
+
+// The walk of a wavefront with RT 16-row tiles from tile t0 (0: only its copies) over the
+// split's pairs, and its rows' outputs.
+template <int D, bool NT, int RT>
+MOLT_DEV void attn_rows_walk(const AttnParams& p, uint8_t* ring, const RowTile& w, int t0, int wave) {
+  constexpr int DS = D / 32;            // 32-dim k-steps for S
+  constexpr int DT = D / 16;            // 16-dim tiles of O^T
+  constexpr int KB = 16 * D * 2;        // bytes of one K (or V) block
+  constexpr int PAIR = 4 * KB;          // K0, K1, V0, V1
+  constexpr int NI = KB / 1024;         // copies per wavefront per pair
+  const int b = w.b, h = w.h, ctx = w.ctx, j0 = w.j0, Rt = w.Rt, r0 = w.r0;
+  const int blk0 = w.blk0, blk1 = w.blk1, npairs = w.npairs;
+  const int G = p.Hq / p.Hkv, kp1 = p.k + 1, R = G * kp1;
+  const int lane = threadIdx.x % kWave, l16 = lane % 16, g4 = lane / 16;
+  const float c = p.scale_log2;
+  const int lim_lo = ctx + j0;          // keys up to here are visible to every row
+  // copies: wavefront w brings block w of the pair; instruction i covers bytes 1024 i .. of it
+  const uint16_t* cache = wave < 2 ? p.kc : p.vc;
+  int voff[NI];
 #pragma unroll
-  for (int i = 0; i < RTW; ++i) {
-    float lt = l_run[i];
-    lt = rows_sum4(lt);
-    const int r = 16 * (rtile + NRT * i) + l16;
-    if (r >= Rt) continue;
-    const int j = j0 + r / G, gi = r % G;
-    // O^T element e of tile dt: dim 16 dt + 4 g4 + e
-    if (p.splits == 1) {
-      const float inv = lt > 0.f ? 1.f / lt : 0.f;
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt) {
-        // the 4 consecutive columns of the lane's rows: one 8-byte store in either layout
-        uint16_t v[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = f32_to_bf16(o[dt][i][e] * inv);
-        *reinterpret_cast<uint2*>(p.out + out_index(p, long(b) * kp1 + j, (h * G + gi) * D + 16 * dt + 4 * g4,
-                                                     long(p.Hq) * D, 2)) =
-            make_uint2(uint32_t(v[0]) | (uint32_t(v[1]) << 16), uint32_t(v[2]) | (uint32_t(v[3]) << 16));
-      }
+  for (int i = 0; i < NI; ++i) {
+    const int ch = i * kWave + lane;            // 16-byte place in the block
+    if (wave < 2) {
+      const int key = ch / (D / 8), s = ch % (D / 8);
+      voff[i] = key * (2 * D) + ((s ^ kswz<D>(key, wave)) * 16);
     } else {
-      const long pr = (long(bh) * p.splits + split) * R + r0 + r;
+      const int dim = ch / 2, s = ch % 2;
+      voff[i] = dim * 32 + ((s ^ vswz(dim)) * 16);
+    }
+  }
+  typedef const __attribute__((address_space(4))) int32_t* ConstInt;
+  const ConstInt btab = (ConstInt)(p.bt + long(b) * p.max_blocks);
+  auto block_id = [&](int pi) __attribute__((always_inline)) {     // of the wavefront's block of pair pi
+    const int rel = 2 * min(pi, npairs - 1) + (wave & 1);
+    return btab[min(blk0 + rel, blk1 - 1)];
+  };
+  auto issue = [&](int pi, int id) __attribute__((always_inline)) {
+    const uint16_t* src = cache + (long(id) * p.Hkv + h) * (16 * D);
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(src), 0, pi < npairs ? KB : 0, kRawRsrcWord3);
+    uint8_t* dst = ring + (pi % kRowStages) * PAIR + wave * KB;
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt) *reinterpret_cast<floatx4_t*>(p.part_o + pr * D + 16 * dt + 4 * g4) = o[dt][i];
-      if (g4 == 0) {
-        p.part_ml[pr * 2 + 0] = m_run[i];
-        p.part_ml[pr * 2 + 1] = lt;
+    for (int i = 0; i < NI; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)(dst + i * 1024), 16,
+                                               voff[i], 0, 0, NT ? 2 : 0);
+  };
+
+  // K fragment: block j = l16 / 8, key 8 ((l16 / 4) % 2) + 4 t + l16 % 4; V fragment: block g4 / 2,
+  // dim 16 dt + l16, chunk g4 % 2 (as in attn_lds_kernel)
+  int koff[DS];
+  {
+    const int j = l16 / 8, key = 8 * ((l16 / 4) % 2) + l16 % 4;
+#pragma unroll
+    for (int s = 0; s < DS; ++s) koff[s] = j * KB + key * (2 * D) + (((4 * s + g4) ^ kswz<D>(key, j)) * 16);
+  }
+  const int vfoff = (2 + g4 / 2) * KB + l16 * 32 + (((g4 % 2) ^ vswz(l16)) * 16);
+
+  constexpr int RA = RT > 0 ? RT : 1;
+  bf16x8_t qf[RA][DS];
+  int lim[RA];
+#pragma unroll
+  for (int i = 0; i < RT; ++i) {
+    const int r = 16 * (t0 + i) + l16;
+    const int j = j0 + r / G, gi = r % G;
+    lim[i] = r < Rt ? ctx + j : -1;
+#pragma unroll
+    for (int s = 0; s < DS; ++s) {
+      if (r < Rt) {
+        qf[i][s] = *reinterpret_cast<const bf16x8_t*>(
+            p.q + ((long(b) * kp1 + j) * p.Hq + h * G + gi) * D + s * 32 + g4 * 8);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) qf[i][s][e] = __bf16(0.f);
       }
     }
   }
+  floatx4_t o[DT][RA];
+  float m_run[RA], l_run[RA];
+#pragma unroll
+  for (int i = 0; i < RT; ++i) {
+    m_run[i] = kNegBig;
+    l_run[i] = 0.f;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) o[dt][i] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  }
+  if (npairs > 0) {
+    int id = block_id(0);
+#pragma unroll
+    for (int u = 0; u < kRowStages - 1; ++u) {
+      issue(u, id);
+      id = block_id(u + 1);
+    }
+    for (int pi = 0; pi < npairs; ++pi) {
+      // this wavefront's copies of pair pi are in (two later pairs may be in flight) and its
+      // reads of pair pi - 1 have returned: after the barrier pair pi is complete for everyone
+      // and the stage of pair pi - 1 takes pair pi + 3
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * NI) : "memory");
+      issue(pi + kRowStages - 1, id);
+      id = block_id(pi + kRowStages);
+      if constexpr (RT > 0) {
+        const int pb = blk0 + 2 * pi;
+        const uint8_t* base = ring + (pi % kRowStages) * PAIR;
+        floatx4_t sv[2][RA];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          bf16x8_t kf[DS];
+#pragma unroll
+          for (int s = 0; s < DS; ++s) kf[s] = *reinterpret_cast<const bf16x8_t*>(base + koff[s] + t * 4 * (2 * D));
+#pragma unroll
+          for (int i = 0; i < RT; ++i) {
+            floatx4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < DS; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[s], qf[i][s], acc, 0, 0, 0);
+            sv[t][i] = acc;
+          }
+        }
+        // lane's 8 keys: block pb + g4 / 2, keys 8 (g4 % 2) + 4 t + e
+        if (!(pb * 16 + 31 <= lim_lo)) {
+          const bool blk_ok = (g4 / 2 == 0) || (pb + 1 < blk1);
+#pragma unroll
+          for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                const int kpos = (pb + g4 / 2) * 16 + 8 * (g4 % 2) + 4 * t + e;
+                if (!(blk_ok && kpos <= lim[i])) sv[t][i][e] = -INFINITY;
+              }
+        }
+        float mx[RA];
+        bool grow = false;
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {
+          float v = fmaxf(fmaxf(fmaxf(sv[0][i][0], sv[0][i][1]), fmaxf(sv[0][i][2], sv[0][i][3])),
+                          fmaxf(fmaxf(sv[1][i][0], sv[1][i][1]), fmaxf(sv[1][i][2], sv[1][i][3])));
+          v = rows_max4(v);
+          mx[i] = v * c;
+          grow |= mx[i] > m_run[i] + kRescaleSlack;
+        }
+        if (__builtin_amdgcn_read_exec() & __ballot(grow)) {
+#pragma unroll
+          for (int i = 0; i < RT; ++i) {
+            const float m_new = fmaxf(m_run[i], mx[i]);
+            const float alpha = __builtin_amdgcn_exp2f(m_run[i] - m_new);
+            l_run[i] *= alpha;
+            m_run[i] = m_new;
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) o[dt][i] *= alpha;
+          }
+        }
+        bf16x8_t pf[RA], pl[RA];   // P = hi + lo
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {
+          const float nm = -m_run[i];
+          float ps = 0.f;
+#pragma unroll
+          for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              // the hardware exp2: a probability under 2^-126 of the row's largest becomes 0
+              const float pe = __builtin_amdgcn_exp2f(fmaf(sv[t][i][e], c, nm));
+              const __bf16 hi = __bf16(pe);
+              pf[i][t * 4 + e] = hi;
+              pl[i][t * 4 + e] = __bf16(pe - float(hi));   // pe - hi is exact in f32
+              ps += pe;
+            }
+          l_run[i] += ps;
+        }
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) {
+          const bf16x8_t vf = *reinterpret_cast<const bf16x8_t*>(base + vfoff + dt * 16 * 32);
+#pragma unroll
+          for (int i = 0; i < RT; ++i) {
+            o[dt][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pf[i], o[dt][i], 0, 0, 0);
+            o[dt][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pl[i], o[dt][i], 0, 0, 0);
+          }
+        }
+      }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no copy may outlive the workgroup
+  }
+  // row totals across the 4 lane groups, then the output (or this split's partials)
+#pragma unroll
+  for (int i = 0; i < RT; ++i) {
+    const float lt = rows_sum4(l_run[i]);
+    const int r = 16 * (t0 + i) + l16;
+    if (r >= Rt) continue;
+    store_row<D>(p, b, h, G, r, r0, j0, R, w.bh, w.split, g4, [&](int dt) { return o[dt][i]; }, m_run[i], lt);
+  }
+}
+
+template <int D, bool NT>
+__global__ __launch_bounds__(kRowWaves * kWave, 2) void attn_rows_kernel(AttnParams p) {
+  __shared__ __attribute__((aligned(16))) uint8_t ring[kRowStages * 4 * 16 * D * 2];   // the only LDS object
+
+  int wi = blockIdx.x;
+  if (p.splits >= 4 && p.qtiles == 1 && (wi | 7) < int(gridDim.x)) wi = (wi & ~7) | ((wi ^ (wi >> 3)) & 7);
+  const int split = wi % p.splits;
+  const int bhn = int(gridDim.x) / p.splits / p.qtiles;
+  // every (b, h)'s last query tile (the most keys) first
+  const int qt = p.qtiles - 1 - wi / p.splits / bhn;
+  const int bh = wi / p.splits % bhn;
+  const int b = bh / p.Hkv, h = bh % p.Hkv;
+  const int G = p.Hq / p.Hkv;
+  const int kp1 = p.k + 1;
+  const int R = G * kp1;
+  const int j0 = qt * p.tq;
+  const int Rt = G * min(p.tq, kp1 - j0);
+  const int r0 = G * j0;
+  const int ctx = p.ctx[b];
+  const int nblk = (ctx + j0 + Rt / G + 15) / 16;
+  const int blk0 = split * p.blocks_per_split;
+  const int blk1 = min(blk0 + p.blocks_per_split, nblk);
+  const int npairs = (blk1 - blk0 + 1) / 2;     // <= 0: an empty split (the merge does not read it)
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  // the wavefront's 16-row tiles [t0, t1)
+  const int ntile = (Rt + 15) / 16;
+  const int t0 = wave * ntile / kRowWaves, t1 = (wave + 1) * ntile / kRowWaves;
+
+  const RowTile w{b, h, bh, split, ctx, j0, Rt, r0, blk0, blk1, npairs};
+  if (t1 - t0 == 2) attn_rows_walk<D, NT, 2>(p, ring, w, t0, wave);
+  else if (t1 - t0 == 1) attn_rows_walk<D, NT, 1>(p, ring, w, t0, wave);
+  else attn_rows_walk<D, NT, 0>(p, ring, w, t0, wave);
 }
 
 // log-sum-exp merge over splits: one workgroup per (b, h, group of 1024 / D rows), each
@@ -566,7 +814,8 @@ hipError_t launch_d(const AttnParams& p, int B, int R, hipStream_t s) {
   const long grid = long(B) * p.Hkv * p.qtiles * p.splits;
   // two key groups when a query tile's row tiles fit half the wavefronts
   if ((Rt + 15) / 16 <= 4) attn_lds_kernel<D, 8, 2><<<grid, 512, 0, s>>>(p);
-  else attn_lds_kernel<D, 8, 1><<<grid, 512, 0, s>>>(p);
+  else if (p.qtiles == 1) attn_rows_kernel<D, true><<<grid, kRowWaves * kWave, 0, s>>>(p);
+  else attn_rows_kernel<D, false><<<grid, kRowWaves * kWave, 0, s>>>(p);
   if (p.splits > 1) attn_merge_kernel<D><<<B * p.Hkv * ((R + 1024 / D - 1) / (1024 / D)), 256, 0, s>>>(p);
   return hipGetLastError();
 }
