@@ -257,7 +257,7 @@ struct MoeWs {
   int32_t* pperm; int32_t* n_padded; int32_t* tiles; int32_t* n_tiles;
   uint8_t* xq; float* xs; void* xt; void* h; uint8_t* hq; float* hs; float* o;
   float* part; long part_elems;   // split-K partial sums of the router GEMM
-  long max_rows; int max_tiles; int tile_m;
+  long max_rows; int max_tiles; molt::MoePlan plan;
 };
 
 // Intermediates of the grouped GEMMs live in padded expert order (each expert's rows start
@@ -268,9 +268,8 @@ struct MoeWs {
 MoeWs carve_moe(molt::Carver& c, int T, int d, int E, int K, int F, molt_dtype act, molt_dtype w) {
   MoeWs m{};
   const long P = long(T) * K;
-  const int tm = molt::moe_tile_m(w, T, K, E);
-  m.tile_m = tm;
-  m.max_tiles = molt::max_expert_tiles(T, E, K, tm);
+  m.plan = molt::moe_plan(w, T, K, E, d, F);
+  m.max_tiles = molt::max_expert_tiles(T, E, K, m.plan.tile_m);
   m.max_rows = molt::max_padded_rows(T, E, K);
   const long R = m.max_rows;
   m.g = c.take<float>(long(T) * E);
@@ -327,7 +326,8 @@ hipError_t run_moe(const MoeWs& m, const void* x, const uint8_t* xq, const float
       return e;
   }
   if ((e = molt::launch_route(nparts > 1 ? m.part : m.g, nparts, bias, replay, T, E, K, m.ids, m.w,
-                              m.counts, m.offsets, m.perm, m.pperm, m.n_padded, m.tile_m,
+                              m.counts, m.offsets, m.perm, m.pperm, m.n_padded,
+                              m.plan.tile_m,
                               m.tiles, m.max_tiles, m.n_tiles, s)) != hipSuccess)
     return e;
   const bool fp8 = wdt == MOLT_FP8_E4M3;
@@ -351,8 +351,8 @@ hipError_t run_moe(const MoeWs& m, const void* x, const uint8_t* xq, const float
     return e;
   {
     ProfScope ps(MOLT_PROF_EXPERT_GEMM, s);
-    if ((e = molt::launch_moe_gate_up(gathered ? m.xt : src, rows ? x_rows : nullptr, xs, m.pperm, K, w_gu, s_gu, d,
-                                      F, wdt, m.tiles, m.n_tiles, m.max_tiles, m.tile_m, m.h,
+    if ((e = molt::launch_moe_gate_up(gathered ? m.xt : src, rows ? x_rows : nullptr, xs, m.pperm, K, w_gu, s_gu, T,
+                                      d, F, wdt, m.tiles, m.n_tiles, m.max_tiles, m.plan, m.h,
                                       s)) != hipSuccess)
       return e;
   }
@@ -364,7 +364,7 @@ hipError_t run_moe(const MoeWs& m, const void* x, const uint8_t* xq, const float
   {
     ProfScope ps(MOLT_PROF_EXPERT_GEMM, s);
     if ((e = molt::launch_moe_down(fp8 ? static_cast<const void*>(m.hq) : m.h, m.hs, m.pperm, w_d,
-                                   s_d, d, F, wdt, m.tiles, m.n_tiles, m.max_tiles, m.tile_m, m.o,
+                                   s_d, d, F, wdt, m.tiles, m.n_tiles, m.max_tiles, m.plan, m.o,
                                    s)) !=
         hipSuccess)
       return e;

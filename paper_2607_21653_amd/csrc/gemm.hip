@@ -456,14 +456,14 @@ void stream_gemm_kernel(GemmParams p) {
 #undef MOLT_GLOAD
 }
 
-// Workgroups of `kernel` (kThreads each) resident on the whole device at once, rounded
+// Workgroups of `kernel` (`threads` each) resident on the whole device at once, rounded
 // down to a multiple of 8 (>= 8).
 template <typename K>
-int resident_grid(K kernel) {
+int resident_grid(K kernel, int threads = kThreads) {
   int dev = 0, cus = 0, per_cu = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kThreads, 0) != hipSuccess)
+      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess)
     return 8;
   return (cus * per_cu) / 8 * 8 > 8 ? (cus * per_cu) / 8 * 8 : 8;
 }
@@ -739,6 +739,8 @@ __global__ __launch_bounds__(128 * WN) void lds_gemm_kernel(GemmParams p, float*
 constexpr int kBigBN = 256;
 constexpr int kBigAStages = 4;
 constexpr int kBigBLoads = 8;                  // weight loads per wavefront per slice
+// weight slices in flight: what the registers hold (two wavefronts a SIMD up to 4 blocks)
+template <int AB> constexpr int kBigDepth = AB == 3 ? 3 : AB == 4 ? 2 : 4;
 
 // Buffer resource word 3 for raw byte-addressed loads (32-bit data format, no swizzle).
 constexpr int kRawRsrcWord3 = 0x00020000;
@@ -756,18 +758,21 @@ MOLT_DEV void lds_dma16(__amdgpu_buffer_rsrc_t r, int voff, int soff, uint8_t* l
 
 // acc[i][j] = rows 32 i .. of the activation tile x the wavefront's column block j over nk K
 // slices. abase / avoff: each lane's source of its 16 bytes of every block's copy (wavefront w
-// copies quarter w); bbase / bvoff: the lane's bytes of its weight blocks. On return no copy is
-// in flight; other wavefronts may still read the ring.
-template <int AB, int DEPTH>
+// copies quarter w); bbase / bvoff: the lane's bytes of its weight blocks. ROWS: the activations
+// are row-major rows; quarter w of a block is its rows 8 w .., and piece s of a row's 128 bytes
+// holds piece s ^ (row / 2 % 8) (conflict-free fragment reads), which the caller's avoff picks.
+// walk: nk rounded up to a multiple of DEPTH; every wavefront of the workgroup has to be given the
+// same walk, it passes 1 + walk barriers. On return no copy is in flight; other wavefronts may still read the ring.
+template <int AB, int DEPTH, bool ROWS = false>
 MOLT_DEV void bigtile_loop(floatx16_t (&acc)[AB][2], uint8_t* ring, const void* abase, int abytes,
                            const int (&avoff)[AB], const void* bbase, int bbytes,
-                           const int (&bvoff)[2], int nk, int wave, int lane) {
+                           const int (&bvoff)[2], int nk, int walk, int wave, int lane) {
   constexpr int kStage = AB * 4096;
   auto issue_a = [&](int kb) __attribute__((always_inline)) {
     const __amdgpu_buffer_rsrc_t ra = raw_rsrc(abase, kb < nk ? abytes : 0);
     uint8_t* dst = ring + (kb % kBigAStages) * kStage + wave * 1024;
 #pragma unroll
-    for (int j = 0; j < AB; ++j) lds_dma16(ra, avoff[j], kb * 4096, dst + j * 4096);
+    for (int j = 0; j < AB; ++j) lds_dma16(ra, avoff[j], kb * (ROWS ? kRowBytes : 4096), dst + j * 4096);
   };
   typedef bf16x8_t BSlice[4][2];   // [k step][column block]
   auto load_b = [&](int kb, BSlice& b) __attribute__((always_inline)) {
@@ -786,9 +791,12 @@ MOLT_DEV void bigtile_loop(floatx16_t (&acc)[AB][2], uint8_t* ring, const void* 
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
   // activation fragments of one k step, two register sets
   bf16x8_t af[2][AB];
-  auto frag = [&](const uint8_t* base, int c, int set) __attribute__((always_inline)) {
+  const unsigned rsw = (4 * (lane / 32)) ^ ((lane % 32 / 2) % 8);
+  const unsigned lbase = ROWS ? (lane % 32) * 128 : lane * 16;
+  auto frag = [&](const uint8_t* stage, int c, int set) __attribute__((always_inline)) {
+    const uint8_t* base = stage + lbase + (ROWS ? (rsw ^ c) * 16 : c * 1024);
 #pragma unroll
-    for (int i = 0; i < AB; ++i) af[set][i] = *reinterpret_cast<const bf16x8_t*>(base + i * 4096 + c * 1024);
+    for (int i = 0; i < AB; ++i) af[set][i] = *reinterpret_cast<const bf16x8_t*>(base + i * 4096);
   };
   auto step = [&](int set, const bf16x8_t (&b)[2]) __attribute__((always_inline)) {
     // the scheduler would otherwise sink the next step's reads below these MFMAs
@@ -807,16 +815,17 @@ MOLT_DEV void bigtile_loop(floatx16_t (&acc)[AB][2], uint8_t* ring, const void* 
   for (int J = 0; J < DEPTH; ++J) load_b(J, bs[J]);
   // slice 0's activations are in (what follows them in the queue may be in flight)
   asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * AB + kBigBLoads * DEPTH) : "memory");
-  frag(ring + lane * 16, 0, 0);
+  frag(ring, 0, 0);
   // Per slice kb the vector-memory queue gets: activations kb + 3 (after the barrier), then
   // weights kb + depth (after the last MFMAs). The barrier of slice kb needs activations
   // kb + 1, issued in slice kb - 2; what may still be in flight behind them is at least
   // weights kb - 2 + depth, activations kb + 2 and weights kb - 1 + depth (exactly that from
   // slice 2 on, more before), so waiting for that many leaves it complete.
   static_assert(DEPTH >= 2, "the first barriers count two weight slices behind the copies");
+  static_assert(2 * AB + kBigBLoads * DEPTH < 64, "vmcnt range");
   constexpr int kAWait = 2 * kBigBLoads + AB;
   auto body = [&](int kb, BSlice& b) __attribute__((always_inline)) {
-    const uint8_t* base = ring + (kb % kBigAStages) * kStage + lane * 16;
+    const uint8_t* base = ring + (kb % kBigAStages) * kStage;
     frag(base, 1, 1);
     step(0, b[0]);
     frag(base, 2, 0);
@@ -828,18 +837,19 @@ MOLT_DEV void bigtile_loop(floatx16_t (&acc)[AB][2], uint8_t* ring, const void* 
     // stage takes slice kb + 3
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(kAWait) : "memory");
     issue_a(kb + 3);
-    frag(ring + ((kb + 1) % kBigAStages) * kStage + lane * 16, 0, 0);
+    frag(ring + ((kb + 1) % kBigAStages) * kStage, 0, 0);
     step(1, b[3]);
     load_b(kb + DEPTH, b);
   };
+  // `walk` slices in whole rounds of DEPTH (register sets are indexed statically): past the last
+  // slice both operands are zeros and add nothing. (Exits between the slices of a round, and around the
+  // loop, made the compiler move all accumulators at each of them, through scratch memory.)
   int kb = 0;
-  for (; kb + DEPTH - 1 < nk; kb += DEPTH) {   // register sets are indexed statically
+  do {
 #pragma unroll
     for (int J = 0; J < DEPTH; ++J) body(kb + J, bs[J]);
-  }
-#pragma unroll
-  for (int J = 0; J < DEPTH - 1; ++J)
-    if (kb + J < nk) body(kb + J, bs[J]);
+    kb += DEPTH;
+  } while (kb < walk);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
@@ -849,8 +859,10 @@ MOLT_DEV void bigtile_loop(floatx16_t (&acc)[AB][2], uint8_t* ring, const void* 
 // bf16 into the idle ring and written from there: q and K rows 16 bytes per store; V heads sit
 // transposed in the ring, so that the lanes of a store are consecutive tokens of one dim. (With
 // V read from rows and each token's cache slot from memory, the few V tiles alone took 40 us.)
-template <int AB, bool ROPE>
+enum BigEpilogue { kBigStore = 0, kBigAdd = 1, kBigRope = 2 };
+template <int AB, int EPI>
 __global__ __launch_bounds__(kThreads, AB <= 4 ? 2 : 1) void bigtile_gemm_kernel(GemmParams p, RopeKv rk) {
+  constexpr bool ROPE = EPI == kBigRope;
   constexpr int BM = 32 * AB;
   // one LDS object (the compiler tells the ring's copies from other reads by their object):
   // the ring, then the cache slots of the tile's rows
@@ -876,9 +888,10 @@ __global__ __launch_bounds__(kThreads, AB <= 4 ? 2 : 1) void bigtile_gemm_kernel
 #pragma unroll
   for (int j = 0; j < 2; ++j) bvoff[j] = int((min(n0 + c0 + 64 * j, last_b) - n0) * RB) + lane * 16;
   floatx16_t acc[AB][2];
-  bigtile_loop<AB, AB == 4 ? 2 : 3>(acc, ring, p.A, int(long(last_a + 32) * RB), avoff,
+  bigtile_loop<AB, kBigDepth<AB>>(acc, ring, p.A, int(long(last_a + 32) * RB), avoff,
                       static_cast<const uint8_t*>(p.B) + long(n0) * RB,
-                      int(long(min(n0 + kBigBN, last_b + 32) - n0) * RB), bvoff, nk, wave, lane);
+                      int(long(min(n0 + kBigBN, last_b + 32) - n0) * RB), bvoff, nk,
+                      (nk + kBigDepth<AB> - 1) / kBigDepth<AB> * kBigDepth<AB>, wave, lane);
   // acc[i][j][e]: row 32 i + 8 (e / 4) + 4 lgrp + e % 4, column c0 + 64 j + lcol
   const int lcol = lane % 32, lgrp = lane / 32;
   if constexpr (ROPE) {
@@ -950,14 +963,14 @@ __global__ __launch_bounds__(kThreads, AB <= 4 ? 2 : 1) void bigtile_gemm_kernel
   float* C = static_cast<float*>(p.C);
   if (row0 + BM <= p.M && n0 + kBigBN <= p.N) {
     // whole tile (all but the last row and column tiles): no bounds checks between the stores
-    // (the LM head: 451 -> 411 us; nontemporal stores measured 420 us), and with accumulate 16
-    // loads ahead of their stores
+    // (the LM head: 451 -> 411 us; nontemporal stores measured 420 us); kBigAdd: 16 loads ahead of
+    // their stores
     float* base = C + long(row0 + 4 * lgrp) * p.ldc + n0 + c0 + lcol;
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int i = 0; i < AB; ++i) {
-        if (p.accumulate) {
+        if (EPI == kBigAdd) {
 #pragma unroll
           for (int e = 0; e < 16; ++e) acc[i][j][e] += base[long(32 * i + 8 * (e / 4) + (e % 4)) * p.ldc + 64 * j];
         }
@@ -977,28 +990,219 @@ __global__ __launch_bounds__(kThreads, AB <= 4 ? 2 : 1) void bigtile_gemm_kernel
         const int grow = row0 + 32 * i + 8 * (e / 4) + 4 * lgrp + (e % 4);
         if (grow >= p.M) continue;
         float* dst = C + long(grow) * p.ldc + col;
-        *dst = p.accumulate ? *dst + acc[i][j][e] : acc[i][j][e];
+        *dst = EPI == kBigAdd ? *dst + acc[i][j][e] : acc[i][j][e];
       }
   }
 }
 
-template <bool ROPE>
+template <int EPI>
 hipError_t run_bigtile(GemmParams p, const RopeKv& rk, int ab, hipStream_t s) {
   p.n_mtiles = (p.M + 32 * ab - 1) / (32 * ab);
   p.n_ntiles = (p.N + kBigBN - 1) / kBigBN;
   const int grid = (p.n_mtiles * p.n_ntiles + 7) / 8 * 8;
   switch (ab) {
-    case 2: bigtile_gemm_kernel<2, ROPE><<<grid, kThreads, 0, s>>>(p, rk); break;
-    case 3: bigtile_gemm_kernel<3, ROPE><<<grid, kThreads, 0, s>>>(p, rk); break;
-    case 4: bigtile_gemm_kernel<4, ROPE><<<grid, kThreads, 0, s>>>(p, rk); break;
+    case 2: bigtile_gemm_kernel<2, EPI><<<grid, kThreads, 0, s>>>(p, rk); break;
+    case 3: bigtile_gemm_kernel<3, EPI><<<grid, kThreads, 0, s>>>(p, rk); break;
+    case 4: bigtile_gemm_kernel<4, EPI><<<grid, kThreads, 0, s>>>(p, rk); break;
     case 5:
-      if constexpr (!ROPE) {
-        bigtile_gemm_kernel<5, false><<<grid, kThreads, 0, s>>>(p, rk);
+      if constexpr (EPI != kBigRope) {
+        bigtile_gemm_kernel<5, EPI><<<grid, kThreads, 0, s>>>(p, rk);
         break;
       }
       [[fallthrough]];
     default: return hipErrorInvalidValue;
   }
+  return hipGetLastError();
+}
+
+// Grouped big-tile expert GEMM (bf16, experts of more than 128 rows): the tile table's tiles have
+// up to 256 rows, the rows of an expert dealt out evenly; n-tiles of 256 weight rows. 8
+// wavefronts, two halves of 4: each half takes half of the tile's 32-row blocks (its own part of
+// the activation ring) against the same weight blocks, wavefront w of both the same columns, so
+// the weights come from HBM once and meet in the CU's L1. (With one workgroup of 4 wavefronts per
+// 128 rows, two a CU, an expert's two row tiles drifted apart by more than the 4 MB of an XCD's
+// L2: the weights were read twice, 1.65 GB for 0.81.) gate_up: a wavefront holds the gate block
+// and the up block of 32 columns, so SwiGLU happens in registers; the product goes through the
+// ring to 16-byte stores. down: 64 columns per wavefront, stored from registers by buffer stores
+// (rows past the tile's end get an offset out of range: no branch between the stores). The main
+// loop is instantiated per number of blocks, so a part-filled tile costs its own blocks only. Each
+// workgroup takes its first tile by its index and the next ones from its XCD's queue, then from
+// the others' (tiles differ in cost, and so do the XCDs' shares).
+constexpr int kGrpBlocks = 4;                  // 32-row blocks of a half, at most
+constexpr int kGrpThreads = 512;
+constexpr int kGrpRing = kBigAStages * kGrpBlocks * 4096;      // one half's ring
+constexpr unsigned kNoRow = 0x80000000u;       // byte offset past every output row
+
+struct GrpLds {                                // after the rings, in the same LDS object
+  unsigned row[2][32 * kGrpBlocks];            // down: byte offset of the row's output
+  int next;
+};
+
+// One half's share of a tile: rows [row0, row1) of the expert, AB blocks (none valid when row1 ==
+// row0). Both halves pass the same barriers.
+template <int AB, int MODE, bool ROWS>
+MOLT_DEV void grouped_tile(const GemmParams& p, uint8_t* lds, int half, int expert, int row0, int row1,
+                           int nt, int wave, int lane) {
+  // the halves of a tile may have different AB: both walk nk rounded up to a multiple of 4
+  constexpr int DEPTH = AB <= 2 ? 4 : 2;
+  static_assert(4 % DEPTH == 0, "both halves pass the same number of barriers");
+  // opaque per tile: the address arithmetic of the instances stays inside the tile loop instead
+  // of being hoisted into registers held across it
+  asm volatile("" : "+v"(lane));
+  uint8_t* ring = lds + half * kGrpRing;
+  unsigned* srow = reinterpret_cast<GrpLds*>(lds + 2 * kGrpRing)->row[half];
+  const int tid = wave * kWave + lane;         // in the half
+  const long RB = 2L * p.K;
+  const int nk = int(RB / kRowBytes);
+  const int lcol = lane % 32, lgrp = lane / 32;
+  const int n0 = nt * (MODE == kGateUp ? 128 : kBigBN);
+  // activations
+  int avoff[AB];
+  const uint8_t* abase = static_cast<const uint8_t*>(p.A);
+  int abytes;
+  if (ROWS) {
+    // the lane's piece of row 8 wave + lane / 8 of each block, of that pair's token row; rows past
+    // the end and padding rows read token 0 (their outputs are not stored)
+    const int rr = 8 * wave + lane / 8;
+#pragma unroll
+    for (int j = 0; j < AB; ++j) {
+      const int r = row0 + 32 * j + rr;
+      const int pr = r < row1 ? p.perm[r] : -1;
+      avoff[j] = (pr < 0 ? 0 : pr / p.ktop) * int(RB) + ((lane % 8) ^ ((rr / 2) % 8)) * 16;
+    }
+    abytes = p.M * int(RB);
+  } else {
+    abase += long(row0) * RB;
+#pragma unroll
+    for (int j = 0; j < AB; ++j) avoff[j] = j * 32 * int(RB) + wave * 1024 + lane * 16;
+    abytes = AB * 32 * int(RB);
+  }
+  // weights: column block j of the wavefront (clamped into the expert's rows; not stored past them)
+  const int rows_e = MODE == kGateUp ? 2 * p.N : p.N;
+  int bcol[2], bvoff[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    bcol[j] = MODE == kGateUp ? n0 + 32 * wave : n0 + 64 * wave + 32 * j;
+    bvoff[j] = (min(bcol[j], p.N - 32) + (MODE == kGateUp ? j * p.N : 0)) * int(RB) + lane * 16;
+  }
+  if (MODE == kDown && tid < 32 * AB) {        // read after the main loop's barriers
+    const int grow = row0 + tid;
+    const int pr = grow < row1 ? p.perm[grow] : -1;
+    srow[tid] = pr < 0 ? kNoRow : unsigned(pr) * unsigned(p.ldc) * 4u;
+  }
+  floatx16_t acc[AB][2];
+  bigtile_loop<AB, DEPTH, ROWS>(acc, ring, abase, abytes, avoff,
+                                static_cast<const uint8_t*>(p.B) + long(expert) * rows_e * RB,
+                                rows_e * int(RB), bvoff, nk, (nk + 3) / 4 * 4, wave, lane);
+  // acc[i][j][e]: row 32 i + 8 (e / 4) + 4 lgrp + e % 4, column bcol[j] + lcol
+  lds_barrier();                               // everyone is done with the rings; the row table is in
+  if (MODE == kGateUp) {
+    uint16_t* ob = reinterpret_cast<uint16_t*>(ring);        // [32 AB][128] bf16
+#pragma unroll
+    for (int i = 0; i < AB; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        __builtin_amdgcn_sched_barrier(0);
+        const int r = 32 * i + 8 * q + 4 * lgrp;
+#pragma unroll
+        for (int u = 0; u < 4; u += 2) {
+          const uint32_t hv = f32x2_to_bf16(silu(acc[i][0][4 * q + u]) * acc[i][1][4 * q + u],
+                                            silu(acc[i][0][4 * q + u + 1]) * acc[i][1][4 * q + u + 1]);
+          ob[(r + u) * 128 + 32 * wave + lcol] = uint16_t(hv);
+          ob[(r + u + 1) * 128 + 32 * wave + lcol] = uint16_t(hv >> 16);
+        }
+      }
+    lds_barrier();
+    const long hrb = 2L * p.N;
+#pragma unroll
+    for (int u = 0; u < 2 * AB; ++u) {
+      const int w = tid + 256 * u, r = w / 16, cb = (w % 16) * 8;
+      if (row0 + r < row1 && n0 + cb < p.N)
+        *reinterpret_cast<int32x4_t*>(static_cast<uint8_t*>(p.C) + tiled_offset(row0 + r, 2L * (n0 + cb), hrb)) =
+            *reinterpret_cast<const int32x4_t*>(ob + r * 128 + cb);
+    }
+  } else {
+    // a wavefront past the last column (N is a multiple of 64): a resource of size 0
+    const __amdgpu_buffer_rsrc_t rc = raw_rsrc(p.C, bcol[0] < p.N ? int(kNoRow - 1u) : 0);
+#pragma unroll
+    for (int i = 0; i < AB; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        __builtin_amdgcn_sched_barrier(0);                   // no more row entries in registers
+        const uint4 ro = *reinterpret_cast<const uint4*>(srow + 32 * i + 8 * q + 4 * lgrp);
+        const unsigned rof[4] = {ro.x, ro.y, ro.z, ro.w};
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            // kNoRow plus a column stays past the resource's end
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[i][j][4 * q + u]), rc,
+                                                  int(rof[u] + unsigned(lcol) * 4u), bcol[j] * 4, 0);
+      }
+  }
+}
+
+template <int MODE, bool ROWS>
+__global__ __launch_bounds__(kGrpThreads, 2) void grouped_bigtile_kernel(GemmParams p) {
+  __shared__ __attribute__((aligned(16))) uint8_t lds[2 * kGrpRing + sizeof(GrpLds)];
+  GrpLds* sh = reinterpret_cast<GrpLds*>(lds + 2 * kGrpRing);
+  const int total = *p.n_tiles_live * p.n_ntiles;
+  const int chunk = (total + 7) / 8;
+  const int stride = gridDim.x / 8;
+  const int xcd = blockIdx.x % 8;
+  const int w8 = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
+  const int half = w8 / 4, wave = w8 % 4;
+  auto pool = [&](int x) { return min(chunk, total - x * chunk); };   // tiles of XCD x (may be <= 0)
+  // the tile after XCD x's first `stride` ones that index k of its queue stands for; -1: past its end
+  auto tile_of = [&](int x, int k) { return stride + k < pool(x) ? x * chunk + stride + k : -1; };
+  auto steal = [&]() {
+    for (int s = 1; s < 8; ++s) {
+      const int x = (xcd + s) % 8;
+      if (pool(x) <= stride) continue;          // all of it was given out by index
+      const int t = tile_of(x, atomicAdd(p.queue + x, 1));
+      if (t >= 0) return t;
+    }
+    return -1;
+  };
+  int id = int(blockIdx.x) / 8 < pool(xcd) ? xcd * chunk + int(blockIdx.x) / 8 : -1;
+  for (;;) {
+    // the next index of the own queue is asked for here and looked at after the tile
+    const bool own = threadIdx.x == 0 && pool(xcd) > stride;
+    int k = 0;
+    if (own) k = atomicAdd(p.queue + xcd, 1);
+    if (id >= 0) {
+      const int mt = id / p.n_ntiles, nt = id % p.n_ntiles;
+      typedef const __attribute__((address_space(4))) int32x4_t* ConstTile;
+      const int32x4_t tv = *(ConstTile)(p.tiles + mt);
+      const int blocks = (tv[2] - tv[1] + 31) / 32, b0 = (blocks + 1) / 2;
+      // rows of this half; the second half of a one-block tile has none and reads the first's
+      const int row0 = half == 0 ? tv[1] : blocks > b0 ? tv[1] + 32 * b0 : tv[1];
+      const int row1 = half == 0 ? min(tv[1] + 32 * b0, tv[2]) : blocks > b0 ? tv[2] : tv[1];
+      switch (half == 0 ? b0 : blocks - b0) {
+        case 0:
+        case 1: grouped_tile<1, MODE, ROWS>(p, lds, half, tv[0], row0, row1, nt, wave, lane); break;
+        case 2: grouped_tile<2, MODE, ROWS>(p, lds, half, tv[0], row0, row1, nt, wave, lane); break;
+        case 3: grouped_tile<3, MODE, ROWS>(p, lds, half, tv[0], row0, row1, nt, wave, lane); break;
+        default: grouped_tile<4, MODE, ROWS>(p, lds, half, tv[0], row0, row1, nt, wave, lane); break;
+      }
+    }
+    if (threadIdx.x == 0) {
+      int t = own ? tile_of(xcd, k) : -1;
+      if (t < 0) t = steal();
+      sh->next = t;
+    }
+    // publishes `next`; everyone is done with the rings and the row table
+    lds_barrier();
+    id = __builtin_amdgcn_readfirstlane(sh->next);
+    if (id < 0) break;
+  }
+}
+
+template <int MODE, bool ROWS>
+hipError_t run_grouped_big(GemmParams p, hipStream_t s) {
+  static const int resident = resident_grid(grouped_bigtile_kernel<MODE, ROWS>, kGrpThreads);
+  const int pairs = (p.n_mtiles * p.n_ntiles + 7) / 8 * 8;   // upper bound of the live pairs
+  grouped_bigtile_kernel<MODE, ROWS><<<pairs < resident ? pairs : resident, kGrpThreads, 0, s>>>(p);
   return hipGetLastError();
 }
 
@@ -1145,12 +1349,20 @@ __global__ __launch_bounds__(kF32Waves * kWave) void f32_gemm_kernel(GemmParams 
 
 }  // namespace
 
-// Row-tile height of the grouped expert GEMMs: large enough that an expert of average load
-// fits one tile (its weights are then streamed once), as small as that allows.
-int moe_tile_m(molt_dtype wdt, int T, int K, int E) {
-  if (wdt == MOLT_F32) return 32;
+// Grouped expert GEMMs. Weight-streaming kernel: row tiles large enough that an expert of average
+// load fits one (its weights are then streamed once), as small as that allows. From 120 rows per
+// expert on average, where many experts need a second 128-row tile, the big-tile kernel takes bf16
+// experts (us gate_up + down at d 2048, F 768, 128 experts top-8, streaming / big-tile: T = 4000
+// 379 + 224 / 275 + 173, 2300 324 + 177 / 191 + 135, 1800 186 + 108 / 175 + 126, 1500 169 + 100 /
+// 167 + 122). fp8 experts stay: their weights are half the bytes, and a version of the big-tile
+// kernel in fp8 measured 125 + 95 against 131 + 93 at 2304 rows with skewed load.
+MoePlan moe_plan(molt_dtype wdt, int T, int K, int E, int d, int F) {
+  if (wdt == MOLT_F32) return {32, false};
   const long avg = (long(T) * K + E - 1) / E;
-  return avg <= 24 ? 32 : avg <= 56 ? 64 : 128;
+  const long lim = 1L << 31;           // 32-bit buffer offsets into each operand
+  if (wdt == MOLT_BF16 && avg >= 120 && 2L * T * d < lim && 4L * T * K * d < lim && 4L * F * d < lim)
+    return {256, true};
+  return {avg <= 24 ? 32 : avg <= 56 ? 64 : 128, false};
 }
 
 // Plan of a dense bf16 GEMM: big tiles of 32 ab rows x 256 columns (ab > 0), or the LDS-tiled
@@ -1215,7 +1427,8 @@ hipError_t launch_gemm(const void* A, const void* Bw, float* C, int M, int N, in
     return run_stream<false, kDown>(p, M <= 32 ? 32 : M <= 64 ? 64 : 128, s);
   }
   const GemmPlan g = gemm_plan(M, N, K, part_elems);
-  if (g.ab > 0) return run_bigtile<false>(p, RopeKv{}, g.ab, s);
+  if (g.ab > 0)
+    return accumulate ? run_bigtile<kBigAdd>(p, RopeKv{}, g.ab, s) : run_bigtile<kBigStore>(p, RopeKv{}, g.ab, s);
   p.n_mtiles = (M + g.bm - 1) / g.bm;
   p.n_ntiles = (N + kBN - 1) / kBN;
   const int grid = (p.n_mtiles * p.n_ntiles * g.splits + 7) / 8 * 8;
@@ -1240,7 +1453,7 @@ hipError_t launch_qkv_rope(const void* A, const void* Bw, int M, int K_in, int H
   RopeKv rk{static_cast<const double2*>(table), kv_slot, Hq, Hkv, static_cast<uint16_t*>(q_out),
             static_cast<uint16_t*>(k_cache), static_cast<uint16_t*>(v_cache)};
   const GemmPlan g = gemm_plan(M, p.N, K_in, 0, true);   // no split: the epilogue needs whole sums
-  if (g.ab > 0) return run_bigtile<true>(p, rk, g.ab, s);
+  if (g.ab > 0) return run_bigtile<kBigRope>(p, rk, g.ab, s);
   p.n_mtiles = (M + g.bm - 1) / g.bm;
   p.n_ntiles = Hq + 2 * Hkv;
   const int grid = (p.n_mtiles * p.n_ntiles + 7) / 8 * 8;
@@ -1251,10 +1464,11 @@ hipError_t launch_qkv_rope(const void* A, const void* Bw, int M, int K_in, int H
 
 hipError_t launch_moe_gate_up(const void* a, const void* a_rows, const float* a_scale,
                               const int32_t* pperm, int K_top, const void* w_gu, const float* s_gu,
-                              int d, int F, molt_dtype wdt, const int32_t* tiles,
-                              const int32_t* n_tiles, int max_tiles, int tile_m, void* h,
+                              int T, int d, int F, molt_dtype wdt, const int32_t* tiles,
+                              const int32_t* n_tiles, int max_tiles, const MoePlan& plan, void* h,
                               hipStream_t s) {
   GemmParams p{};
+  p.M = T;
   p.n_tiles_live = n_tiles;
   p.A = a_rows != nullptr && wdt != MOLT_F32 ? a_rows : a;
   p.B = w_gu; p.C = h; p.N = F; p.K = d; p.ldc = F;
@@ -1267,16 +1481,21 @@ hipError_t launch_moe_gate_up(const void* a, const void* a_rows, const float* a_
     f32_gemm_kernel<kGateUp><<<max_tiles * p.n_ntiles, kF32Waves * kWave, 0, s>>>(p);
     return hipGetLastError();
   }
-  p.n_ntiles = F / (kBN / 2);
   p.queue = const_cast<int32_t*>(n_tiles) + 1;
-  if (wdt == MOLT_FP8_E4M3) return run_stream<true, kGateUp>(p, tile_m, s, a_rows != nullptr);
-  return run_stream<false, kGateUp>(p, tile_m, s, a_rows != nullptr);
+  const bool rows = a_rows != nullptr;
+  if (plan.big) {
+    p.n_ntiles = (F + 127) / 128;
+    return rows ? run_grouped_big<kGateUp, true>(p, s) : hipErrorInvalidValue;   // bf16 callers have rows
+  }
+  p.n_ntiles = F / (kBN / 2);
+  if (wdt == MOLT_FP8_E4M3) return run_stream<true, kGateUp>(p, plan.tile_m, s, rows);
+  return run_stream<false, kGateUp>(p, plan.tile_m, s, rows);
 }
 
 hipError_t launch_moe_down(const void* a, const float* a_scale, const int32_t* pperm,
                            const void* w_d, const float* s_d, int d, int F, molt_dtype wdt,
                            const int32_t* tiles, const int32_t* n_tiles, int max_tiles,
-                           int tile_m, float* o, hipStream_t s) {
+                           const MoePlan& plan, float* o, hipStream_t s) {
   GemmParams p{};
   p.n_tiles_live = n_tiles;
   p.A = a; p.B = w_d; p.C = o; p.N = d; p.K = F; p.ldc = d;
@@ -1289,10 +1508,14 @@ hipError_t launch_moe_down(const void* a, const float* a_scale, const int32_t* p
     f32_gemm_kernel<kDown><<<max_tiles * p.n_ntiles, kF32Waves * kWave, 0, s>>>(p);
     return hipGetLastError();
   }
-  p.n_ntiles = d / kBN;
   p.queue = const_cast<int32_t*>(n_tiles) + 1 + kTileQueues;
-  if (wdt == MOLT_FP8_E4M3) return run_stream<true, kDown>(p, tile_m, s);
-  return run_stream<false, kDown>(p, tile_m, s);
+  if (plan.big) {
+    p.n_ntiles = (d + kBigBN - 1) / kBigBN;
+    return run_grouped_big<kDown, false>(p, s);
+  }
+  p.n_ntiles = d / kBN;
+  if (wdt == MOLT_FP8_E4M3) return run_stream<true, kDown>(p, plan.tile_m, s);
+  return run_stream<false, kDown>(p, plan.tile_m, s);
 }
 
 hipError_t launch_pack_tiled(const void* src, void* dst, long rows, long row_bytes, hipStream_t s) {

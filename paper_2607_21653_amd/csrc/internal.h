@@ -129,6 +129,9 @@ hipError_t launch_gemm(const void* A, const void* Bw, float* C, int M, int N, in
 hipError_t launch_qkv_rope(const void* A, const void* Bw, int M, int K_in, int Hq, int Hkv,
                            const void* table, const int32_t* kv_slot, void* q_out, void* k_cache,
                            void* v_cache, hipStream_t s);
+// Row-tile height of the tile table, and which kernel takes it (big: the big-tile one)
+struct MoePlan { int tile_m; bool big; };
+MoePlan moe_plan(molt_dtype wdt, int T, int K, int E, int d, int F);
 // Grouped expert GEMMs over the tile table built by launch_route. bf16/fp8: A and the
 // weights in the tiled layout, gate_up writes h tiled; f32: the same, gate_up's a is the
 // tiled token rows, read through pperm. Rows are padded-order; down writes o[pair]. gate_up with a_rows (the token
@@ -136,13 +139,13 @@ hipError_t launch_qkv_rope(const void* A, const void* Bw, int M, int K_in, int H
 // pperm instead of the gathered copy a.
 hipError_t launch_moe_gate_up(const void* a, const void* a_rows, const float* a_scale,
                               const int32_t* pperm, int K_top, const void* w_gu, const float* s_gu,
-                              int d, int F, molt_dtype wdt, const int32_t* tiles,
-                              const int32_t* n_tiles, int max_tiles, int tile_m, void* h,
+                              int T, int d, int F, molt_dtype wdt, const int32_t* tiles,
+                              const int32_t* n_tiles, int max_tiles, const MoePlan& plan, void* h,
                               hipStream_t s);
 hipError_t launch_moe_down(const void* a, const float* a_scale, const int32_t* pperm,
                            const void* w_d, const float* s_d, int d, int F, molt_dtype wdt,
                            const int32_t* tiles, const int32_t* n_tiles, int max_tiles,
-                           int tile_m, float* o, hipStream_t s);
+                           const MoePlan& plan, float* o, hipStream_t s);
 // row-major [rows, row_bytes] -> tiled layout (row_bytes % 128 == 0), rows padded to a
 // multiple of 32 with zeros
 hipError_t launch_pack_tiled(const void* src, void* dst, long rows, long row_bytes, hipStream_t s);
@@ -151,7 +154,6 @@ hipError_t launch_pack_tiled(const void* src, void* dst, long rows, long row_byt
 hipError_t launch_gather_tiled(const void* src, const int32_t* pperm, int K_top,
                                const int32_t* n_rows, long max_rows, long row_bytes, void* dst,
                                hipStream_t s);
-int moe_tile_m(molt_dtype wdt, int T, int K, int E);
 
 // ------------------------------------------------------------- attention
 size_t attention_ws_bytes(int B, int k, int Hq, int Hkv, int D, int max_blocks);

@@ -248,8 +248,14 @@ __global__ __launch_bounds__(kPermThreads) void permute_kernel(PermuteParams p) 
     if (tid < p.E) {
       p.counts[tid] = c;
       p.offsets[tid] = off[tid];
-      for (int m0 = 0, i = v[2]; m0 < c && i < p.max_tiles; m0 += p.tile_m, ++i)
-        p.tiles[i] = make_int4(tid, poff[tid] + m0, poff[tid] + min(m0 + p.tile_m, c), 0);
+      // the expert's 32-row blocks dealt out evenly over its tiles (9 blocks in tiles of at most
+      // 4: 3 + 3 + 3, so that no tile streams the weights for one block)
+      const int blocks = (c + 31) / 32;
+      for (int u = 0, m0 = 0; u < tn && v[2] + u < p.max_tiles; ++u) {
+        const int m1 = m0 + 32 * (blocks / tn + (u < blocks % tn ? 1 : 0));
+        p.tiles[v[2] + u] = make_int4(tid, poff[tid] + m0, poff[tid] + min(m1, c), 0);
+        m0 = m1;
+      }
       for (int r = poff[tid] + c; r < poff[tid + 1]; ++r) p.pperm[r] = -1;
     }
     if (tid == 0) {
