@@ -52,6 +52,27 @@ MOLT_DEV float key_value(unsigned long long key) {
   return __uint_as_float((ord >> 31) ? (ord & 0x7fffffffu) : ~ord);
 }
 
+// router logit e of a token (g: its row of split 0): the split-K partial sums of the router GEMM
+// added in split order, all loads in flight together (a loop over a run-time number of splits
+// waited for each in turn: top-K of 5..80 tokens 7.4 us, now 5.0)
+template <int NP>
+MOLT_DEV float sum_parts(const float* g, long stride) {
+  float v[NP];
+#pragma unroll
+  for (int s = 0; s < NP; ++s) v[s] = g[s * stride];
+#pragma unroll
+  for (int s = 1; s < NP; ++s) v[0] += v[s];
+  return v[0];
+}
+template <int NP>
+MOLT_DEV void load_logits(const float* gt, long stride, int lane, int E, float (&g)[4]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int e = lane + kWave * i;
+    g[i] = e < E ? sum_parts<NP>(gt + e, stride) : 0.f;
+  }
+}
+
 __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ logits, int nparts,
                                                    const float* __restrict__ bias,
                                                    const int32_t* __restrict__ replay, int T, int E,
@@ -60,12 +81,10 @@ __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ log
   const int t = blockIdx.x * 4 + threadIdx.x / kWave;
   const int lane = threadIdx.x % kWave;
   if (t >= T) return;
-  // router logit: the split-K partial sums of the router GEMM added in split order
   const float* gt = logits + long(t) * E;
   const long stride = long(T) * E;
   auto gval = [&](int e) {
     float v = gt[e];
-#pragma unroll 8
     for (int s = 1; s < nparts; ++s) v += gt[s * stride + e];
     return v;
   };
@@ -80,10 +99,19 @@ __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ log
     }
   } else {
     unsigned long long key[4];
+    float g[4];
+    if (nparts == 8) load_logits<8>(gt, stride, lane, E, g);
+    else if (nparts == 4) load_logits<4>(gt, stride, lane, E, g);
+    else if (nparts == 2) load_logits<2>(gt, stride, lane, E, g);
+    else if (nparts == 1) load_logits<1>(gt, stride, lane, E, g);
+    else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) g[i] = lane + kWave * i < E ? gval(lane + kWave * i) : 0.f;
+    }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int e = lane + kWave * i;
-      key[i] = e < E ? route_key(gval(e) + (bias ? bias[e] : 0.f), e) : 0ull;
+      key[i] = e < E ? route_key(g[i] + (bias ? bias[e] : 0.f), e) : 0ull;
     }
     for (int j = 0; j < K; ++j) {
       unsigned long long mine = key[0];
@@ -297,7 +325,6 @@ hipError_t launch_route(const float* logits, int nparts, const float* bias, cons
                         int32_t* offsets, int32_t* perm, int32_t* pperm, int32_t* n_padded,
                         int tile_m, int32_t* tiles, int max_tiles, int32_t* n_tiles,
                         hipStream_t s) {
-  topk_kernel<<<(T + 3) / 4, 256, 0, s>>>(logits, nparts, bias, replay, T, E, K, ids, w);
   PermuteParams p;
   p.ids = ids;
   p.P = T * K;
@@ -314,6 +341,7 @@ hipError_t launch_route(const float* logits, int nparts, const float* bias, cons
   p.tiles = reinterpret_cast<int4*>(tiles);
   p.max_tiles = max_tiles;
   p.n_tiles = n_tiles;
+  topk_kernel<<<(T + 3) / 4, 256, 0, s>>>(logits, nparts, bias, replay, T, E, K, ids, w);
   permute_kernel<<<(p.P + p.range - 1) / p.range, kPermThreads, 0, s>>>(p);
   return hipGetLastError();
 }
