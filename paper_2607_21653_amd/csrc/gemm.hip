@@ -717,6 +717,111 @@ __global__ __launch_bounds__(128 * WN) void lds_gemm_kernel(GemmParams p, float*
   }
 }
 
+// ---------------------------------------------------------------- few-row QKV projection
+// At up to 128 rows the QKV projection is the latency of its K walk: 40 column tiles x 32 slices,
+// one after the other, on 40 workgroups (15 us at 5 rows for 21 MB of weights). Here a workgroup
+// takes 32 columns of a head, the rotation pairs (i, i + 64) of 16 dims, x 32 AB rows, and its 8
+// wavefronts split the K slices: at K = 2048 each has 4, all loaded at once straight into MFMA
+// operand registers (weights and the tiled activations alike), so the walk is one memory latency;
+// the 8 partial tiles meet in LDS and are added in wavefront order (deterministic). The epilogue
+// has a rotation pair per thread. Measured (us, LDS-tiled / this): 5 rows 15.4 / 7.2, 48 rows
+// 17.3 / 10.2, 80 rows 18.0 / 15.4; at 128 rows the layer gains 1 us, at 192 none, at 256 it loses 5.
+constexpr int kFewWaves = 8;
+constexpr int kFewSlices = 4;                 // slices of a wavefront in flight
+constexpr int kFewRows = 128;
+
+template <int AB>
+__global__ __launch_bounds__(kFewWaves * kWave, 2) void qkv_few_kernel(GemmParams p, RopeKv rk) {
+  __shared__ float red[kFewWaves][AB][1024];
+  const int h = blockIdx.x / 4, i0 = 16 * (blockIdx.x % 4), row0 = 32 * AB * blockIdx.y;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
+  const int nk = p.K / 64, l32 = lane % 32;
+  const bool rotate = h < rk.Hq + rk.Hkv;
+  // the thread's outputs: pair c (dims i0 + c, i0 + c + 64) of row r0 + 32 u
+  const int c = threadIdx.x % 16, r0 = threadIdx.x / 16;
+  double2 cs[AB];
+  int slot[AB];
+#pragma unroll
+  for (int u = 0; u < AB; ++u) {
+    const int t = min(row0 + r0 + 32 * u, p.M - 1);
+    cs[u] = rotate ? rk.table[long(t) * 64 + i0 + c] : make_double2(1.0, 0.0);
+    slot[u] = rk.slot[t];
+  }
+  // weight row of the lane: dim i0 + l (l < 16), then i0 + 64 + l - 16
+  const int brow = h * 128 + i0 + (l32 < 16 ? l32 : 48 + l32);
+  const long RB = 2L * p.K;
+  const uint8_t* b = static_cast<const uint8_t*>(p.B) + tiled_offset(brow, 64 * (lane / 32), RB);
+  const uint8_t* a[AB];
+#pragma unroll
+  for (int i = 0; i < AB; ++i) a[i] = static_cast<const uint8_t*>(p.A) + long(min(row0 + 32 * i, (p.M - 1) & ~31)) * RB + lane * 16;
+  floatx16_t acc[AB];
+#pragma unroll
+  for (int i = 0; i < AB; ++i)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[i][e] = 0.f;
+  auto walk = [&](auto& bv, auto& av, int kb, int n) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < n; ++s)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const long off = long(kb + kFewWaves * s) * 4096 + q * 1024;
+        bv[s][q] = __builtin_nontemporal_load(reinterpret_cast<const int32x4_t*>(b + off));
+#pragma unroll
+        for (int i = 0; i < AB; ++i) av[s][q][i] = *reinterpret_cast<const int32x4_t*>(a[i] + off);
+      }
+    __builtin_amdgcn_sched_barrier(0);        // all loads before the first MFMA waits for one
+#pragma unroll
+    for (int s = 0; s < n; ++s)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int i = 0; i < AB; ++i)
+          acc[i] = mfma(__builtin_bit_cast(bf16x8_t, av[s][q][i]), __builtin_bit_cast(bf16x8_t, bv[s][q]), acc[i]);
+  };
+  int32x4_t bv[kFewSlices][4], av[kFewSlices][4][AB];
+  int kb = wave;
+  for (; kb + kFewWaves * (kFewSlices - 1) < nk; kb += kFewWaves * kFewSlices) walk(bv, av, kb, kFewSlices);
+  for (; kb < nk; kb += kFewWaves) walk(bv, av, kb, 1);
+#pragma unroll
+  for (int i = 0; i < AB; ++i)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) red[wave][i][e * kWave + lane] = acc[i][e];
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < AB; ++u) {
+    // row r0 of block u sits at element 4 (r0 / 8) + r0 % 4 of lanes 32 (r0 / 4 % 2) + column
+    const int at = (4 * (r0 / 8) + r0 % 4) * kWave + 32 * (r0 / 4 % 2) + c;
+    float lo = red[0][u][at], hi = red[0][u][at + 16];
+#pragma unroll
+    for (int w = 1; w < kFewWaves; ++w) {
+      lo += red[w][u][at];
+      hi += red[w][u][at + 16];
+    }
+    const int t = row0 + r0 + 32 * u, sl = slot[u];
+    if (t >= p.M) continue;
+    if (rotate) {
+      const double x = lo, y = hi;
+      lo = float(x * cs[u].x - y * cs[u].y);
+      hi = float(y * cs[u].x + x * cs[u].y);
+    }
+    uint16_t* dst;
+    long step = 64;
+    if (h < rk.Hq) {
+      dst = rk.q + (long(t) * rk.Hq + h) * 128 + i0 + c;
+    } else {
+      if (sl < 0) continue;
+      if (rotate) {
+        dst = rk.kc + ((long(sl >> 4) * rk.Hkv + (h - rk.Hq)) * 16 + (sl & 15)) * 128 + i0 + c;
+      } else {
+        dst = rk.vc + ((long(sl >> 4) * rk.Hkv + (h - rk.Hq - rk.Hkv)) * 128 + i0 + c) * 16 + (sl & 15);
+        step = 64 * 16;
+      }
+    }
+    dst[0] = f32_to_bf16(lo);
+    dst[step] = f32_to_bf16(hi);
+  }
+}
+
 // ---------------------------------------------------------------- big-tile GEMM
 // GEMMs with many rows and columns are bound by what the memory pipeline can hand the MFMAs,
 // so their tile is sized for flops per loaded byte: 32 AB rows x 256 columns per workgroup
@@ -1452,6 +1557,12 @@ hipError_t launch_qkv_rope(const void* A, const void* Bw, int M, int K_in, int H
   p.A = A; p.B = Bw; p.M = M; p.N = (Hq + 2 * Hkv) * 128; p.K = K_in; p.ldc = p.N;
   RopeKv rk{static_cast<const double2*>(table), kv_slot, Hq, Hkv, static_cast<uint16_t*>(q_out),
             static_cast<uint16_t*>(k_cache), static_cast<uint16_t*>(v_cache)};
+  if (M <= kFewRows) {
+    const int nt = 4 * (Hq + 2 * Hkv);
+    if (M <= 32) qkv_few_kernel<1><<<dim3(nt, 1), kFewWaves * kWave, 0, s>>>(p, rk);
+    else qkv_few_kernel<2><<<dim3(nt, (M + 63) / 64), kFewWaves * kWave, 0, s>>>(p, rk);
+    return hipGetLastError();
+  }
   const GemmPlan g = gemm_plan(M, p.N, K_in, 0, true);   // no split: the epilogue needs whole sums
   if (g.ab > 0) return run_bigtile<kBigRope>(p, rk, g.ab, s);
   p.n_mtiles = (M + g.bm - 1) / g.bm;
