@@ -587,10 +587,11 @@ hipError_t run_decoder(const DecWs& w, const molt_model* m, const molt_kv* kv, i
   const bool fp8 = m->expert_dtype == MOLT_FP8_E4M3;
   hipError_t e = hipSuccess;
 #define RUN(call) do { if ((e = (call)) != hipSuccess) return e; } while (0)
-  RUN(molt::launch_rope_table(kv->context_lens, B, k, D, m->rope_theta, w.rope, kv->block_tables,
-                              kv->max_blocks_per_seq, kv->num_blocks, w.kv_slot, s));
+  const molt::RopeTable rope{kv->context_lens, k, D, m->rope_theta, w.rope, kv->block_tables,
+                             kv->max_blocks_per_seq, kv->num_blocks, w.kv_slot};
   RUN(molt::launch_residual_norm(x, nullptr, 0, nullptr, nullptr, 0, m->attn_norm[0], T, d,
-                                 m->rms_eps, m->dtype, w.y, nullptr, nullptr, s));
+                                 m->rms_eps, m->dtype, w.y, nullptr, nullptr, s, nullptr, nullptr,
+                                 &rope));
   for (int l = 0; l < L; ++l) {
     if (m->dtype == MOLT_BF16 && D == 128) {
       // one 128-column tile per head: RoPE and the KV-cache write in the GEMM epilogue

@@ -32,6 +32,24 @@ __global__ __launch_bounds__(kThreads) void embed_kernel(const void* __restrict_
     x[long(t) * d + i] = ok ? load_act(table, long(tok) * d + i, dt) : 0.f;
 }
 
+// RoPE angle table of the step: token t = b*(1+k)+j sits at position ctx[b]+j; pair i
+// (i, i+D/2) turns by position * theta^(-2i/D); cos and sin evaluated in f64, once per step
+// for all layers. table[t][i] = {cos, sin}; with kv_slot also the token's KV-cache slot.
+MOLT_DEV void rope_table_row(const RopeTable& r, int t) {
+  const int b = t / (r.k + 1);
+  const long pos = long(r.ctx[b]) + t % (r.k + 1);
+  if (r.kv_slot && threadIdx.x == 0) {
+    const int blk = r.bt[long(b) * r.max_blocks + pos / 16];
+    r.kv_slot[t] = blk >= 0 && blk < r.num_blocks ? blk * 16 + int(pos % 16) : -1;
+  }
+  double2* table = static_cast<double2*>(r.table);
+  for (int i = threadIdx.x; i < r.D / 2; i += kThreads) {
+    const double inv_freq = pow(double(r.theta), -2.0 * double(i) / double(r.D));
+    const double ang = double(pos) * inv_freq;
+    table[long(t) * (r.D / 2) + i] = make_double2(cos(ang), sin(ang));
+  }
+}
+
 // Residual update and RMSNorm of token row t, fused:
 //   x[t] += part[0][t] + part[1][t] + ...   (split-K partial sums of the O projection, in
 //                                            split order; nparts = 0: none)
@@ -42,7 +60,8 @@ __global__ __launch_bounds__(kThreads) void embed_kernel(const void* __restrict_
 // GEMM through the permutation).
 // Each thread owns runs of 8 consecutive elements (d % 8 == 0, d <= 8 * 256 * kNormRuns),
 // kept in registers from the residual update to the stores: one 16-byte store of y per run
-// (8 bf16 are contiguous in the tiled layout).
+// (8 bf16 are contiguous in the tiled layout). Workgroups past the T rows write the step's RoPE
+// table, one token each: the first norm of a step carries it (a launch of its own took 4-5 us).
 constexpr int kNormRuns = 8;
 
 template <typename T>
@@ -57,9 +76,14 @@ __global__ __launch_bounds__(kThreads) void residual_norm_kernel(
     float* __restrict__ x, const float* __restrict__ part, int nparts, long part_stride,
     const float* __restrict__ o, const float* __restrict__ w, int K, const float* __restrict__ g,
     int d, float eps, molt_dtype dt, void* __restrict__ y, uint8_t* __restrict__ yq,
-    float* __restrict__ ys, void* __restrict__ y_rows, uint8_t* __restrict__ yq_rows) {
+    float* __restrict__ ys, void* __restrict__ y_rows, uint8_t* __restrict__ yq_rows, int T,
+    RopeTable rope) {
   __shared__ float red[kThreads / kWave];
   const int t = blockIdx.x;
+  if (t >= T) {
+    rope_table_row(rope, t - T);
+    return;
+  }
   float* xr = x + long(t) * d;
   float v[kNormRuns][8];
   // the gains are loaded with x: loaded after the x stores, they would wait for those
@@ -211,26 +235,6 @@ __global__ __launch_bounds__(kThreads) void quant_rows_tiled_kernel(
   if (s > kFastDivMinScale) encode_all([&](float x) { return div_by_scale(x, s, rs); });
   else encode_all([&](float x) { return x / s; });
   if (lane == 0) scale[r] = s;
-}
-
-// RoPE angle table of the step: token t = b*(1+k)+j sits at position ctx[b]+j; pair i
-// (i, i+D/2) turns by position * theta^(-2i/D); cos and sin evaluated in f64, once per step
-// for all layers. table[t][i] = {cos, sin}.
-__global__ __launch_bounds__(kThreads) void rope_table_kernel(
-    const int32_t* __restrict__ ctx, int k, int D, float theta, double2* __restrict__ table,
-    const int32_t* __restrict__ bt, int max_blocks, int num_blocks, int32_t* __restrict__ kv_slot) {
-  const int t = blockIdx.x;
-  const int b = t / (k + 1);
-  const long pos = long(ctx[b]) + t % (k + 1);
-  if (kv_slot && threadIdx.x == 0) {
-    const int blk = bt[long(b) * max_blocks + pos / 16];
-    kv_slot[t] = blk >= 0 && blk < num_blocks ? blk * 16 + int(pos % 16) : -1;
-  }
-  for (int i = threadIdx.x; i < D / 2; i += kThreads) {
-    const double inv_freq = pow(double(theta), -2.0 * double(i) / double(D));
-    const double ang = double(pos) * inv_freq;
-    table[long(t) * (D / 2) + i] = make_double2(cos(ang), sin(ang));
-  }
 }
 
 // RoPE on q and k of token t (rotation in f64 with the step's table), then
@@ -437,18 +441,10 @@ hipError_t launch_embed(const void* table, const int32_t* tokens, int T, int d, 
 hipError_t launch_residual_norm(float* x, const float* part, int nparts, const float* o,
                                 const float* w, int K, const float* g, int T, int d, float eps,
                                 molt_dtype dt, void* y, uint8_t* yq, float* ys, hipStream_t s,
-                                void* y_rows, uint8_t* yq_rows) {
-  residual_norm_kernel<<<T, kThreads, 0, s>>>(x, part, nparts, long(T) * d, o, w, K, g, d, eps, dt,
-                                              y, yq, ys, dt == MOLT_BF16 ? y_rows : nullptr,
-                                              yq ? yq_rows : nullptr);
-  return hipGetLastError();
-}
-
-hipError_t launch_rope_table(const int32_t* ctx, int B, int k, int D, float theta, void* table,
-                             const int32_t* bt, int max_blocks, int num_blocks, int32_t* kv_slot,
-                             hipStream_t s) {
-  rope_table_kernel<<<B * (k + 1), kThreads, 0, s>>>(ctx, k, D, theta, static_cast<double2*>(table),
-                                                     bt, max_blocks, num_blocks, kv_slot);
+                                void* y_rows, uint8_t* yq_rows, const RopeTable* rope) {
+  residual_norm_kernel<<<rope ? 2 * T : T, kThreads, 0, s>>>(
+      x, part, nparts, long(T) * d, o, w, K, g, d, eps, dt, y, yq, ys,
+      dt == MOLT_BF16 ? y_rows : nullptr, yq ? yq_rows : nullptr, T, rope ? *rope : RopeTable{});
   return hipGetLastError();
 }
 

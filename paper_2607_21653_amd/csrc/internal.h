@@ -49,21 +49,23 @@ hipError_t launch_draft_draw(const float* logits, int B, int V, const float* u, 
 // ------------------------------------------------------------- elementwise
 hipError_t launch_embed(const void* table, const int32_t* tokens, int T, int d, int V,
                         molt_dtype dt, float* x, hipStream_t s);
+// RoPE cos/sin of the step's B*(1+k) positions (f64 pairs, [T, D/2]), shared by all layers;
+// with kv_slot also each token's KV-cache slot (block * 16 + position % 16, -1 when the block
+// table entry is out of range)
+struct RopeTable {
+  const int32_t* ctx; int k, D; float theta; void* table;
+  const int32_t* bt; int max_blocks, num_blocks; int32_t* kv_slot;
+};
 // x[t] += sum of nparts split-K partials (part[s * T * d ..], split order) and, with o, the
 // MoE combine sum_j w[t, j] o[t * K + j]; then with g: y = rmsnorm(x) * g in act dtype,
 // tiled layout (rows padded to 32 by the caller's allocation), optionally with its fp8
 // row codes (tiled) and scales, and row-major copies of y (y_rows, bf16) and of its codes
-// (yq_rows)
+// (yq_rows); with rope also the step's RoPE table (of the same T tokens)
 hipError_t launch_residual_norm(float* x, const float* part, int nparts, const float* o,
                                 const float* w, int K, const float* g, int T, int d, float eps,
                                 molt_dtype dt, void* y, uint8_t* yq, float* ys, hipStream_t s,
-                                void* y_rows = nullptr, uint8_t* yq_rows = nullptr);
-// RoPE cos/sin of the step's B*(1+k) positions (f64 pairs, [T, D/2]), shared by all layers;
-// with kv_slot also each token's KV-cache slot (block * 16 + position % 16, -1 when the block
-// table entry is out of range)
-hipError_t launch_rope_table(const int32_t* ctx, int B, int k, int D, float theta, void* table,
-                             const int32_t* bt, int max_blocks, int num_blocks, int32_t* kv_slot,
-                             hipStream_t s);
+                                void* y_rows = nullptr, uint8_t* yq_rows = nullptr,
+                                const RopeTable* rope = nullptr);
 hipError_t launch_rope_kv_write(const float* qkv, int B, int k, int Hq, int Hkv, int D,
                                 const void* table, const int32_t* ctx, const int32_t* bt,
                                 int max_blocks, int num_blocks, molt_dtype dt, void* q_out,
