@@ -167,6 +167,23 @@ MOLT_DEV unsigned long long wave_max_dpp(unsigned long long v) {
   return (static_cast<unsigned long long>(lane63(uint32_t(v >> 32))) << 32) | lane63(uint32_t(v));
 }
 
+// unsigned 64-bit sum over the wavefront (every lane gets it; integers: exact)
+template <int CTRL, int ROWS>
+MOLT_DEV unsigned long long dpp_sum_step(unsigned long long v) {
+  const uint32_t lo = dpp_u32<CTRL, ROWS>(uint32_t(v), 0u);
+  const uint32_t hi = dpp_u32<CTRL, ROWS>(uint32_t(v >> 32), 0u);
+  return v + ((static_cast<unsigned long long>(hi) << 32) | lo);
+}
+MOLT_DEV unsigned long long wave_sum_dpp(unsigned long long v) {
+  v = dpp_sum_step<0x111, 0xF>(v);
+  v = dpp_sum_step<0x112, 0xF>(v);
+  v = dpp_sum_step<0x114, 0xF>(v);
+  v = dpp_sum_step<0x118, 0xF>(v);
+  v = dpp_sum_step<0x142, 0xA>(v);
+  v = dpp_sum_step<0x143, 0xC>(v);
+  return (static_cast<unsigned long long>(lane63(uint32_t(v >> 32))) << 32) | lane63(uint32_t(v));
+}
+
 MOLT_DEV float wave_max_dpp(float v) {
   v = dpp_max_step<0x111, 0xF>(v);
   v = dpp_max_step<0x112, 0xF>(v);
