@@ -255,16 +255,15 @@ long gemm_part_elems(int M, int N, int K, molt_dtype dt) {
 struct MoeWs {
   float* g; int32_t* ids; float* w; int32_t* counts; int32_t* offsets; int32_t* perm;
   int32_t* pperm; int32_t* n_padded; int32_t* tiles; int32_t* n_tiles;
-  uint8_t* xq; float* xs; void* xt; void* h; uint8_t* hq; float* hs; float* o;
+  uint8_t* xq; float* xs; void* h; uint8_t* hq; float* hs; float* o;
   float* part; long part_elems;   // split-K partial sums of the router GEMM
   long max_rows; int max_tiles; molt::MoePlan plan;
 };
 
 // Intermediates of the grouped GEMMs live in padded expert order (each expert's rows start
-// at a multiple of 32), tiled: the gathered activations xt (expert dtype), the SwiGLU
-// product h (act dtype) and its fp8 codes hq/hs. xq/xs: fp8 codes of the input when the
-// caller has none. The per-pair expert outputs o are row-major in pair order (token * K +
-// slot).
+// at a multiple of 32), tiled: the SwiGLU product h (act dtype) and its fp8 codes hq/hs. xq/xs:
+// row-major fp8 codes of the input when the caller has none. The per-pair expert outputs o are
+// row-major in pair order (token * K + slot).
 MoeWs carve_moe(molt::Carver& c, int T, int d, int E, int K, int F, molt_dtype act, molt_dtype w) {
   MoeWs m{};
   const long P = long(T) * K;
@@ -288,7 +287,6 @@ MoeWs carve_moe(molt::Carver& c, int T, int d, int E, int K, int F, molt_dtype a
     m.hq = c.take<uint8_t>(R * F);
     m.hs = c.take<float>(R);
   }
-  m.xt = c.take<uint8_t>(w == MOLT_F32 ? 0 : R * d * dt_size(w));
   m.h = c.take<uint8_t>(R * F * dt_size(act));
   m.o = c.take<float>(P * d);
   m.part_elems = gemm_part_elems(T, E, d, act);
@@ -308,15 +306,15 @@ int moe_shape_ok(int T, int d, int E, int K, int F, molt_dtype act, molt_dtype w
   return MOLT_OK;
 }
 
-// Enqueues the MoE layer on normalised input x (act dtype, tiled, rows padded to 32; xq/xs =
-// its tiled fp8 codes when the caller already quantised them). Router and expert weights
-// tiled. With out: out = sum (accumulate: out += sum); without, the per-pair expert outputs
-// m.o and route weights m.w are left for the caller to combine.
-hipError_t run_moe(const MoeWs& m, const void* x, const uint8_t* xq, const float* xs,
+// Enqueues the MoE layer on normalised input x (act dtype, tiled, rows padded to 32; x_rows = its
+// rows row-major, or with xs their fp8 codes and scales; not needed in f32). Router and expert
+// weights tiled. With out: out = sum (accumulate: out += sum); without, the per-pair expert
+// outputs m.o and route weights m.w are left for the caller to combine.
+hipError_t run_moe(const MoeWs& m, const void* x, const void* x_rows, const float* xs,
                    const void* w_router, const float* bias, const void* w_gu, const void* w_d,
                    const float* s_gu, const float* s_d, int T, int d, int E, int K, int F,
                    molt_dtype act, molt_dtype wdt, const int32_t* replay, float* out,
-                   bool accumulate, hipStream_t s, const void* x_rows = nullptr) {
+                   bool accumulate, hipStream_t s) {
   hipError_t e;
   int nparts = 1;
   {
@@ -331,29 +329,20 @@ hipError_t run_moe(const MoeWs& m, const void* x, const uint8_t* xq, const float
                               m.tiles, m.max_tiles, m.n_tiles, s)) != hipSuccess)
     return e;
   const bool fp8 = wdt == MOLT_FP8_E4M3;
-  const bool xq_given = xq != nullptr;
-  if (fp8 && xq == nullptr) {
-    if ((e = molt::launch_quant_rows_tiled(static_cast<const uint16_t*>(x), nullptr, nullptr, T, d,
-                                           m.xq, m.xs, s)) != hipSuccess)
+  // gate_up's rows: the tiled x for f32, else row-major: x itself, or its fp8 codes, which the
+  // caller has already (x_rows with xs) or which are made here from x
+  const void* src = wdt == MOLT_F32 ? x : x_rows;
+  if (fp8 && xs == nullptr) {
+    if ((e = molt::launch_quant_rows(static_cast<const uint16_t*>(x_rows), T, d, m.xq, m.xs, s)) !=
+        hipSuccess)
       return e;
-    xq = m.xq;
+    src = m.xq;
     xs = m.xs;
   }
-  // row-major token rows at hand (bf16 rows of x for bf16 experts, the caller's fp8 codes
-  // for fp8 experts): gate_up reads them through the permutation, no gathered copy
-  const bool rows = x_rows != nullptr &&
-                    (wdt == MOLT_BF16 ? act == MOLT_BF16 : wdt == MOLT_FP8_E4M3 && xq_given);
-  // (f32 experts read the tiled token rows themselves through the permutation)
-  const void* src = fp8 ? static_cast<const void*>(xq) : x;
-  const bool gathered = !rows && wdt != MOLT_F32;
-  if (gathered && (e = molt::launch_gather_tiled(src, m.pperm, K, m.n_padded, m.max_rows,
-                                              long(d) * dt_size(wdt), m.xt, s)) != hipSuccess)
-    return e;
   {
     ProfScope ps(MOLT_PROF_EXPERT_GEMM, s);
-    if ((e = molt::launch_moe_gate_up(gathered ? m.xt : src, rows ? x_rows : nullptr, xs, m.pperm, K, w_gu, s_gu, T,
-                                      d, F, wdt, m.tiles, m.n_tiles, m.max_tiles, m.plan, m.h,
-                                      s)) != hipSuccess)
+    if ((e = molt::launch_moe_gate_up(src, xs, m.pperm, K, w_gu, s_gu, T, d, F, wdt, m.tiles,
+                                      m.n_tiles, m.max_tiles, m.plan, m.h, s)) != hipSuccess)
       return e;
   }
   if (fp8) {
@@ -410,8 +399,8 @@ int molt_moe_layer(const void* x, const void* w_router, const float* router_bias
   MoeWs m = carve_moe(c, T, d, E, K, F, act_dtype, w_dtype);
   hipError_t e = molt::launch_pack_tiled(x, xt, T, long(d) * dt_size(act_dtype), s);
   if (e == hipSuccess)
-    e = run_moe(m, xt, nullptr, nullptr, w_router, router_bias, w_gate_up, w_down, s_gate_up,
-                s_down, T, d, E, K, F, act_dtype, w_dtype, replay_ids, out, false, s, x);
+    e = run_moe(m, xt, x, nullptr, w_router, router_bias, w_gate_up, w_down, s_gate_up, s_down, T,
+                d, E, K, F, act_dtype, w_dtype, replay_ids, out, false, s);
   const size_t P = size_t(T) * K;
   if (e == hipSuccess) e = copy_out(out_ids, m.ids, P * 4, s);
   if (e == hipSuccess) e = copy_out(out_weights, m.w, P * 4, s);
@@ -538,7 +527,7 @@ int model_ok(const molt_model* m, const molt_kv* kv, int B, int k, bool need_hea
 }
 
 struct DecWs {
-  void* y; uint8_t* yq; float* ys; float* qkv; void* q; void* attn; void* attn_ws; MoeWs moe;
+  void* y; float* ys; float* qkv; void* q; void* attn; void* attn_ws; MoeWs moe;
   void* y_rows;                   // the pre-MoE y row-major (bf16 experts) or its fp8 codes
                                   // row-major (fp8 experts): the expert GEMM's input
   float* part; long part_elems;   // split-K partial sums of the QKV and O projections
@@ -554,7 +543,6 @@ DecWs carve_dec(molt::Carver& c, const molt_model* m, int B, int k, int max_bloc
   const long Tp = pad32(T);                 // GEMM operands: tiled, rows padded to 32
   w.y = c.take<uint8_t>(Tp * d * es);
   if (m->expert_dtype == MOLT_FP8_E4M3) {
-    w.yq = c.take<uint8_t>(Tp * d);
     w.ys = c.take<float>(Tp);
   }
   if (m->dtype == MOLT_BF16 && m->expert_dtype == MOLT_BF16) w.y_rows = c.take<uint8_t>(T * d * es);
@@ -590,8 +578,7 @@ hipError_t run_decoder(const DecWs& w, const molt_model* m, const molt_kv* kv, i
   const molt::RopeTable rope{kv->context_lens, k, D, m->rope_theta, w.rope, kv->block_tables,
                              kv->max_blocks_per_seq, kv->num_blocks, w.kv_slot};
   RUN(molt::launch_residual_norm(x, nullptr, 0, nullptr, nullptr, 0, m->attn_norm[0], T, d,
-                                 m->rms_eps, m->dtype, w.y, nullptr, nullptr, s, nullptr, nullptr,
-                                 &rope));
+                                 m->rms_eps, m->dtype, w.y, s, nullptr, nullptr, nullptr, &rope));
   for (int l = 0; l < L; ++l) {
     if (m->dtype == MOLT_BF16 && D == 128) {
       // one 128-column tile per head: RoPE and the KV-cache write in the GEMM epilogue
@@ -622,21 +609,21 @@ hipError_t run_decoder(const DecWs& w, const molt_model* m, const molt_kv* kv, i
     }
     // x += O partials; y = RMSNorm(x) * moe_norm (+ fp8 codes)
     RUN(molt::launch_residual_norm(x, np > 1 ? w.part : nullptr, np > 1 ? np : 0, nullptr, nullptr,
-                                   0, m->moe_norm[l], T, d, m->rms_eps, m->dtype, w.y,
-                                   fp8 ? w.yq : nullptr, fp8 ? w.ys : nullptr, s,
+                                   0, m->moe_norm[l], T, d, m->rms_eps, m->dtype, w.y, s,
                                    fp8 ? nullptr : w.y_rows,
-                                   fp8 ? static_cast<uint8_t*>(w.y_rows) : nullptr));
-    RUN(run_moe(w.moe, w.y, fp8 ? w.yq : nullptr, fp8 ? w.ys : nullptr, m->w_router[l],
+                                   fp8 ? static_cast<uint8_t*>(w.y_rows) : nullptr,
+                                   fp8 ? w.ys : nullptr));
+    RUN(run_moe(w.moe, w.y, w.y_rows, fp8 ? w.ys : nullptr, m->w_router[l],
                 m->router_bias ? m->router_bias[l] : nullptr, m->w_gate_up[l], m->w_down[l],
                 fp8 ? m->s_gate_up[l] : nullptr, fp8 ? m->s_down[l] : nullptr, T, d,
                 m->n_experts, K, m->d_ff, m->dtype, m->expert_dtype,
-                replay ? replay + size_t(l) * T * K : nullptr, nullptr, false, s, w.y_rows));
+                replay ? replay + size_t(l) * T * K : nullptr, nullptr, false, s));
     if (routes) RUN(copy_out(routes + size_t(l) * T * K, w.moe.ids, size_t(T) * K * 4, s));
     // x += MoE combine; then the next layer's attention norm (or the final norm)
     const bool last = l + 1 == L;
     RUN(molt::launch_residual_norm(x, nullptr, 0, w.moe.o, w.moe.w, K,
                                    last ? final_g : m->attn_norm[l + 1], T, d, m->rms_eps,
-                                   m->dtype, last ? final_y : w.y, nullptr, nullptr, s));
+                                   m->dtype, last ? final_y : w.y, s));
   }
 #undef RUN
   return e;

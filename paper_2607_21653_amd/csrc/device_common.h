@@ -304,7 +304,7 @@ MOLT_DEV float silu(float x) {
 }
 
 // ---------------------------------------------------------------- tiled operand layout
-// The grouped expert GEMMs keep their operands (expert weights, gathered activations, the
+// The grouped expert GEMMs keep their operands (expert weights, the
 // SwiGLU product) in a tiled byte layout. A row-major matrix of R rows (R % 32 == 0) and
 // RB bytes per row (RB % 128 == 0) is cut into 32-row x 128-byte tiles; tile (rb, kb) is
 // the 4 KB at ((rb * RB / 128) + kb) * 4096, and byte j of row r inside it sits at

@@ -55,9 +55,9 @@ MOLT_DEV void rope_table_row(const RopeTable& r, int t) {
 //                                            split order; nparts = 0: none)
 //   x[t] += sum_j w[t, j] * o[t * K + j]     (MoE combine, slot order; o = NULL: none)
 //   y = x[t] / sqrt(mean(x[t]^2) + eps) * g  rounded to dt, tiled (g = NULL: no norm)
-// With yq, also the per-row fp8 code of y (s = amax|y| / 448, code = e4m3(y / s)); with
-// y_rows (bf16) and yq_rows, also y and its codes in row-major order (read by the expert
-// GEMM through the permutation).
+// With yq_rows, also the per-row fp8 code of y (s = amax|y| / 448, code = e4m3(y / s)) in
+// row-major order, with y_rows (bf16) y itself (read by the expert GEMM through the
+// permutation).
 // Each thread owns runs of 8 consecutive elements (d % 8 == 0, d <= 8 * 256 * kNormRuns),
 // kept in registers from the residual update to the stores: one 16-byte store of y per run
 // (8 bf16 are contiguous in the tiled layout). Workgroups past the T rows write the step's RoPE
@@ -75,9 +75,8 @@ MOLT_DEV void add8(float (&v)[8], const T* src, float wgt) {
 __global__ __launch_bounds__(kThreads) void residual_norm_kernel(
     float* __restrict__ x, const float* __restrict__ part, int nparts, long part_stride,
     const float* __restrict__ o, const float* __restrict__ w, int K, const float* __restrict__ g,
-    int d, float eps, molt_dtype dt, void* __restrict__ y, uint8_t* __restrict__ yq,
-    float* __restrict__ ys, void* __restrict__ y_rows, uint8_t* __restrict__ yq_rows, int T,
-    RopeTable rope) {
+    int d, float eps, molt_dtype dt, void* __restrict__ y, float* __restrict__ ys,
+    void* __restrict__ y_rows, uint8_t* __restrict__ yq_rows, int T, RopeTable rope) {
   __shared__ float red[kThreads / kWave];
   const int t = blockIdx.x;
   if (t >= T) {
@@ -153,7 +152,7 @@ __global__ __launch_bounds__(kThreads) void residual_norm_kernel(
           make_float4(v[r][4], v[r][5], v[r][6], v[r][7]);
     }
   }
-  if (yq == nullptr) return;
+  if (yq_rows == nullptr) return;
   amax = block_max_dpp<kThreads / kWave>(amax, red);
   const float sc = amax / 448.0f;
   // v / sc: IEEE for tiny scales, else the reciprocal with one fma correction (same codes;
@@ -169,8 +168,7 @@ __global__ __launch_bounds__(kThreads) void residual_norm_kernel(
 #pragma unroll
         for (int e = 0; e < 8; e += 2) c[e / 4] |= f32x2_to_fp8e4m3(div(v[r][e]), div(v[r][e + 1])) << (8 * (e % 4));
       }
-      *reinterpret_cast<uint2*>(yq + tiled_offset(t, i, d)) = make_uint2(c[0], c[1]);
-      if (yq_rows) *reinterpret_cast<uint2*>(yq_rows + long(t) * d + i) = make_uint2(c[0], c[1]);
+      *reinterpret_cast<uint2*>(yq_rows + long(t) * d + i) = make_uint2(c[0], c[1]);
     }
   };
   if (sc > kFastDivMinScale) codes([&](float x) { return div_by_scale(x, sc, rsc); });
@@ -181,11 +179,13 @@ __global__ __launch_bounds__(kThreads) void residual_norm_kernel(
 // Per-row fp8 quantisation of tiled bf16 rows into tiled e4m3 codes (s = amax / 448,
 // code = e4m3(v / s), zero row -> s = 0): the SwiGLU product of the grouped GEMMs (rows in
 // padded expert order, count on the device, padding rows with pair -1 get zero codes and
-// scale 0) or an input activation (all `rows` rows). One wavefront per row; lane l holds
+// scale 0); or, without kTiled, of row-major rows into row-major codes: an input activation (all
+// `rows` rows; the expert GEMM reads its rows through the permutation). One wavefront per row; lane l holds
 // the 4-column chunks l, l + 64, ... in registers from the amax to the codes (the row is
 // read once; rows past 64 * kQuantRegChunks * 4 columns re-read the rest).
 constexpr int kQuantRegChunks = 16;
-__global__ __launch_bounds__(kThreads) void quant_rows_tiled_kernel(
+template <bool kTiled>
+__global__ __launch_bounds__(kThreads) void quant_rows_kernel(
     const uint16_t* __restrict__ h, const int32_t* __restrict__ pperm,
     const int32_t* __restrict__ n_rows, long rows, int cols, uint8_t* __restrict__ q,
     float* __restrict__ scale) {
@@ -197,7 +197,7 @@ __global__ __launch_bounds__(kThreads) void quant_rows_tiled_kernel(
   const uint8_t* hb = reinterpret_cast<const uint8_t*>(h);
   const int nch = cols / 4;                  // 4-column chunks of the row
   auto load = [&](int ch) __attribute__((always_inline)) {
-    return *reinterpret_cast<const uint2*>(hb + tiled_offset(r, 8L * ch, rb_in));
+    return *reinterpret_cast<const uint2*>(hb + (kTiled ? tiled_offset(r, 8L * ch, rb_in) : r * rb_in + 8L * ch));
   };
   uint2 reg[kQuantRegChunks];
   float amax = 0.f;
@@ -222,7 +222,7 @@ __global__ __launch_bounds__(kThreads) void quant_rows_tiled_kernel(
     if (s > 0.f)
       code = f32x2_to_fp8e4m3(div(bf16_to_f32(uint16_t(v.x))), div(bf16_to_f32(uint16_t(v.x >> 16)))) |
              (f32x2_to_fp8e4m3(div(bf16_to_f32(uint16_t(v.y))), div(bf16_to_f32(uint16_t(v.y >> 16)))) << 16);
-    *reinterpret_cast<uint32_t*>(q + tiled_offset(r, 4L * ch, rb_out)) = code;
+    *reinterpret_cast<uint32_t*>(q + (kTiled ? tiled_offset(r, 4L * ch, rb_out) : r * rb_out + 4L * ch)) = code;
   };
   auto encode_all = [&](auto div) __attribute__((always_inline)) {
 #pragma unroll
@@ -440,11 +440,11 @@ hipError_t launch_embed(const void* table, const int32_t* tokens, int T, int d, 
 
 hipError_t launch_residual_norm(float* x, const float* part, int nparts, const float* o,
                                 const float* w, int K, const float* g, int T, int d, float eps,
-                                molt_dtype dt, void* y, uint8_t* yq, float* ys, hipStream_t s,
-                                void* y_rows, uint8_t* yq_rows, const RopeTable* rope) {
+                                molt_dtype dt, void* y, hipStream_t s, void* y_rows,
+                                uint8_t* yq_rows, float* ys, const RopeTable* rope) {
   residual_norm_kernel<<<rope ? 2 * T : T, kThreads, 0, s>>>(
-      x, part, nparts, long(T) * d, o, w, K, g, d, eps, dt, y, yq, ys,
-      dt == MOLT_BF16 ? y_rows : nullptr, yq ? yq_rows : nullptr, T, rope ? *rope : RopeTable{});
+      x, part, nparts, long(T) * d, o, w, K, g, d, eps, dt, y, ys,
+      dt == MOLT_BF16 ? y_rows : nullptr, yq_rows, T, rope ? *rope : RopeTable{});
   return hipGetLastError();
 }
 
@@ -465,7 +465,15 @@ hipError_t launch_quant_rows_tiled(const uint16_t* h, const int32_t* pperm, cons
   constexpr int rows_per_block = kThreads / kWave;
   const long grid = (max_rows + rows_per_block - 1) / rows_per_block;
   if (grid == 0) return hipSuccess;
-  quant_rows_tiled_kernel<<<grid, kThreads, 0, s>>>(h, pperm, n_rows, max_rows, cols, q, scale);
+  quant_rows_kernel<true><<<grid, kThreads, 0, s>>>(h, pperm, n_rows, max_rows, cols, q, scale);
+  return hipGetLastError();
+}
+
+hipError_t launch_quant_rows(const uint16_t* x, long rows, int cols, uint8_t* q, float* scale,
+                             hipStream_t s) {
+  constexpr int rows_per_block = kThreads / kWave;
+  quant_rows_kernel<false><<<(rows + rows_per_block - 1) / rows_per_block, kThreads, 0, s>>>(
+      x, nullptr, nullptr, rows, cols, q, scale);
   return hipGetLastError();
 }
 

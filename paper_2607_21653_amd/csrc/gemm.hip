@@ -26,7 +26,7 @@ enum Mode { kDense = 0, kGateUp = 1, kDown = 2 };
 constexpr int kWaitVmcnt0 = (7 << 4) | (15 << 8);
 
 struct GemmParams {
-  const void* A;           // tiled. dense: [M, K]; gate_up: gathered rows [R, K]; down: h [R, K]
+  const void* A;           // dense: [M, K] tiled; gate_up: token rows, row-major; down: h [R, K] tiled
   const void* B;           // tiled. dense: [N, K]; gate_up: [E, 2F, K]; down: [E, N, K]
   void* C;                 // dense: f32 [M, ldc]; gate_up: h tiled [R, F]; down: f32 [P, ldc]
   int M, N, K;             // N: output columns (gate_up: F)
@@ -484,15 +484,13 @@ hipError_t run_stream_k(GemmParams p, int tile_m, hipStream_t s) {
 }
 
 template <bool FP8, int MODE>
-hipError_t run_stream(GemmParams p, int tile_m, hipStream_t s, bool rows = false) {
+hipError_t run_stream(GemmParams p, int tile_m, hipStream_t s) {
   const long nk = long(p.K) * (FP8 ? 1 : 2) / kRowBytes;
   // chained in bf16 for down only: its 12-slice tiles gained (85 -> 82 us per launch at
   // T*K = 5120), gate_up's 32-slice tiles did not (159 -> 161 us)
   if constexpr (!FP8 && MODE == kDown)
     if (nk % 4 == 0) return run_stream_k<false, MODE, true>(p, tile_m, s);
-  if constexpr (MODE == kGateUp)
-    if (rows) return run_stream_k<FP8, MODE, false, true>(p, tile_m, s);
-  return run_stream_k<FP8, MODE, false>(p, tile_m, s);
+  return run_stream_k<FP8, MODE, false, MODE == kGateUp>(p, tile_m, s);
 }
 
 // ---------------------------------------------------------------- LDS-tiled dense GEMM
@@ -1338,27 +1336,6 @@ __global__ __launch_bounds__(kThreads) void pack_tiled_kernel(const uint8_t* __r
   *reinterpret_cast<int4*>(dst + tiled_offset(r, j, RB)) = v;
 }
 
-// gather: tiled activation rows in padded expert order from tiled token rows,
-// row = src[pperm[row] / ktop]; one workgroup per 4 KB tile of the destination, thread =
-// 16-byte chunk of it. Padding rows are left unwritten: a GEMM output row depends on its
-// own operand row only, and the rows computed from padding are never stored. (Workgroups
-// over 8 slices of a 32-row block, each thread with 8 loads in flight, took twice as long.)
-__global__ __launch_bounds__(kThreads) void gather_tiled_kernel(
-    const uint8_t* __restrict__ src, const int32_t* __restrict__ pperm, int ktop,
-    const int32_t* __restrict__ n_rows, long RB, uint8_t* __restrict__ dst) {
-  const long tile = blockIdx.x;
-  const long nk = RB / 128;
-  const long rb = tile / nk, kb = tile % nk;
-  if (rb * 32 >= *n_rows) return;
-  const int quarter = threadIdx.x / 64, l = threadIdx.x % 64;
-  const long row = rb * 32 + (l % 32);
-  const long j = kb * 128 + (l / 32) * 64 + quarter * 16;
-  const int pair = pperm[row];
-  if (pair < 0) return;
-  *reinterpret_cast<int4*>(dst + tile * 4096 + threadIdx.x * 16) =
-      *reinterpret_cast<const int4*>(src + tiled_offset(pair / ktop, j, RB));
-}
-
 // ---------------------------------------------------------------- f32 MFMA path
 // The f32 model on v_mfma_f32_32x32x2_f32 (f32 products, f32 accumulation). Workgroup = one
 // 32 x 32 output tile (gate_up: its gate and its up tile), 8 wavefronts that split the K
@@ -1573,15 +1550,14 @@ hipError_t launch_qkv_rope(const void* A, const void* Bw, int M, int K_in, int H
   return hipGetLastError();
 }
 
-hipError_t launch_moe_gate_up(const void* a, const void* a_rows, const float* a_scale,
-                              const int32_t* pperm, int K_top, const void* w_gu, const float* s_gu,
-                              int T, int d, int F, molt_dtype wdt, const int32_t* tiles,
-                              const int32_t* n_tiles, int max_tiles, const MoePlan& plan, void* h,
-                              hipStream_t s) {
+hipError_t launch_moe_gate_up(const void* a, const float* a_scale, const int32_t* pperm, int K_top,
+                              const void* w_gu, const float* s_gu, int T, int d, int F,
+                              molt_dtype wdt, const int32_t* tiles, const int32_t* n_tiles,
+                              int max_tiles, const MoePlan& plan, void* h, hipStream_t s) {
   GemmParams p{};
   p.M = T;
   p.n_tiles_live = n_tiles;
-  p.A = a_rows != nullptr && wdt != MOLT_F32 ? a_rows : a;
+  p.A = a;
   p.B = w_gu; p.C = h; p.N = F; p.K = d; p.ldc = F;
   p.tiles = reinterpret_cast<const int4*>(tiles);
   p.n_mtiles = max_tiles;
@@ -1593,14 +1569,13 @@ hipError_t launch_moe_gate_up(const void* a, const void* a_rows, const float* a_
     return hipGetLastError();
   }
   p.queue = const_cast<int32_t*>(n_tiles) + 1;
-  const bool rows = a_rows != nullptr;
   if (plan.big) {
     p.n_ntiles = (F + 127) / 128;
-    return rows ? run_grouped_big<kGateUp, true>(p, s) : hipErrorInvalidValue;   // bf16 callers have rows
+    return run_grouped_big<kGateUp, true>(p, s);
   }
   p.n_ntiles = F / (kBN / 2);
-  if (wdt == MOLT_FP8_E4M3) return run_stream<true, kGateUp>(p, plan.tile_m, s, rows);
-  return run_stream<false, kGateUp>(p, plan.tile_m, s, rows);
+  if (wdt == MOLT_FP8_E4M3) return run_stream<true, kGateUp>(p, plan.tile_m, s);
+  return run_stream<false, kGateUp>(p, plan.tile_m, s);
 }
 
 hipError_t launch_moe_down(const void* a, const float* a_scale, const int32_t* pperm,
@@ -1634,16 +1609,6 @@ hipError_t launch_pack_tiled(const void* src, void* dst, long rows, long row_byt
   if (chunks == 0) return hipSuccess;
   pack_tiled_kernel<<<(chunks + kThreads - 1) / kThreads, kThreads, 0, s>>>(
       static_cast<const uint8_t*>(src), static_cast<uint8_t*>(dst), rows, row_bytes);
-  return hipGetLastError();
-}
-
-hipError_t launch_gather_tiled(const void* src, const int32_t* pperm, int K_top,
-                               const int32_t* n_rows, long max_rows, long row_bytes, void* dst,
-                               hipStream_t s) {
-  const long tiles = max_rows / 32 * (row_bytes / 128);
-  if (tiles == 0) return hipSuccess;
-  gather_tiled_kernel<<<tiles, kThreads, 0, s>>>(static_cast<const uint8_t*>(src), pperm, K_top,
-                                                 n_rows, row_bytes, static_cast<uint8_t*>(dst));
   return hipGetLastError();
 }
 

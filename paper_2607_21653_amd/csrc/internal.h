@@ -58,23 +58,25 @@ struct RopeTable {
 };
 // x[t] += sum of nparts split-K partials (part[s * T * d ..], split order) and, with o, the
 // MoE combine sum_j w[t, j] o[t * K + j]; then with g: y = rmsnorm(x) * g in act dtype,
-// tiled layout (rows padded to 32 by the caller's allocation), optionally with its fp8
-// row codes (tiled) and scales, and row-major copies of y (y_rows, bf16) and of its codes
-// (yq_rows); with rope also the step's RoPE table (of the same T tokens)
+// tiled layout (rows padded to 32 by the caller's allocation), optionally with a row-major copy
+// of y (y_rows, bf16) or its row-major fp8 row codes (yq_rows) and scales (ys); with rope also the step's RoPE table (of the same T tokens)
 hipError_t launch_residual_norm(float* x, const float* part, int nparts, const float* o,
                                 const float* w, int K, const float* g, int T, int d, float eps,
-                                molt_dtype dt, void* y, uint8_t* yq, float* ys, hipStream_t s,
-                                void* y_rows = nullptr, uint8_t* yq_rows = nullptr,
+                                molt_dtype dt, void* y, hipStream_t s, void* y_rows = nullptr,
+                                uint8_t* yq_rows = nullptr, float* ys = nullptr,
                                 const RopeTable* rope = nullptr);
 hipError_t launch_rope_kv_write(const float* qkv, int B, int k, int Hq, int Hkv, int D,
                                 const void* table, const int32_t* ctx, const int32_t* bt,
                                 int max_blocks, int num_blocks, molt_dtype dt, void* q_out,
                                 void* k_cache, void* v_cache, hipStream_t s);
-// fp8 rows of a tiled bf16 matrix: rows = *n_rows when n_rows is given (padded expert
-// order, pperm marks padding rows), else max_rows
+// fp8 rows of a tiled bf16 matrix, tiled codes: rows = *n_rows (padded expert order, pperm marks
+// padding rows)
 hipError_t launch_quant_rows_tiled(const uint16_t* h, const int32_t* pperm, const int32_t* n_rows,
                                    long max_rows, int cols, uint8_t* q, float* scale,
                                    hipStream_t s);
+// fp8 rows of a row-major bf16 matrix, row-major codes
+hipError_t launch_quant_rows(const uint16_t* x, long rows, int cols, uint8_t* q, float* scale,
+                             hipStream_t s);
 // out[t] (+)= sum_j w[t, j] o[t * K + j]
 hipError_t launch_combine(const float* o, const float* w, int T, int K, int d, float* out,
                           bool accumulate, hipStream_t s);
@@ -134,14 +136,11 @@ hipError_t launch_qkv_rope(const void* A, const void* Bw, int M, int K_in, int H
 // Row-tile height of the tile table, and which kernel takes it (big: the big-tile one)
 struct MoePlan { int tile_m; bool big; };
 MoePlan moe_plan(molt_dtype wdt, int T, int K, int E, int d, int F);
-// Grouped expert GEMMs over the tile table built by launch_route. bf16/fp8: A and the
-// weights in the tiled layout, gate_up writes h tiled; f32: the same, gate_up's a is the
-// tiled token rows, read through pperm. Rows are padded-order; down writes o[pair]. gate_up with a_rows (the token
-// rows in the expert dtype, row-major [T, K]) reads each padded row's token row through
-// pperm instead of the gathered copy a.
-hipError_t launch_moe_gate_up(const void* a, const void* a_rows, const float* a_scale,
-                              const int32_t* pperm, int K_top, const void* w_gu, const float* s_gu,
-                              int T, int d, int F, molt_dtype wdt, const int32_t* tiles,
+// Grouped expert GEMMs over the tile table built by launch_route. gate_up reads each padded row's
+// token row through pperm: a = the token rows in the expert dtype, row-major [T, K] (f32: tiled);
+// weights, h and down's a in the tiled layout, rows of h in padded order; down writes o[pair].
+hipError_t launch_moe_gate_up(const void* a, const float* a_scale, const int32_t* pperm,
+                              int K_top, const void* w_gu, const float* s_gu, int T, int d, int F, molt_dtype wdt, const int32_t* tiles,
                               const int32_t* n_tiles, int max_tiles, const MoePlan& plan, void* h,
                               hipStream_t s);
 hipError_t launch_moe_down(const void* a, const float* a_scale, const int32_t* pperm,
@@ -151,12 +150,6 @@ hipError_t launch_moe_down(const void* a, const float* a_scale, const int32_t* p
 // row-major [rows, row_bytes] -> tiled layout (row_bytes % 128 == 0), rows padded to a
 // multiple of 32 with zeros
 hipError_t launch_pack_tiled(const void* src, void* dst, long rows, long row_bytes, hipStream_t s);
-// tiled rows in padded expert order from tiled token rows: row = src[pperm[row] / K_top];
-// padding rows are left unwritten
-hipError_t launch_gather_tiled(const void* src, const int32_t* pperm, int K_top,
-                               const int32_t* n_rows, long max_rows, long row_bytes, void* dst,
-                               hipStream_t s);
-
 // ------------------------------------------------------------- attention
 size_t attention_ws_bytes(int B, int k, int Hq, int Hkv, int D, int max_blocks);
 // out [T, Hq*D] row-major, or tiled (rows padded to 32 by the caller) with out_tiled
