@@ -813,15 +813,15 @@ __global__ __launch_bounds__(kF32AttnWaves * kWave) void attn_f32_kernel(
 }
 
 // Splits of the key range: enough workgroups to fill the chip twice over (512), each split a
-// multiple of 8 blocks and at least 32 blocks long, or, where that leaves the chip half empty (a
-// few sequences of short contexts), at least 8: there a split's time is its chain of steps (one
-// sequence at context 1500, 4 kv heads: 12 workgroups of 32 blocks 20 us, 48 of 8 15 us, both
-// with the merge).
+// multiple of 8 blocks and at least 32 blocks long, or, where that leaves three quarters of the chip
+// empty (a few sequences of short contexts), at least 8: there a split's time is its chain of steps
+// (us with the merge, splits of 32 / 8 blocks: one sequence at context 1500 20 / 15, 4 at 300..600
+// 19.6 / 15.7; with 120 and 240 workgroups, 30 at 300..600 21.5 / 25.4 and 60 at 100..300 23 / 33).
 void split_plan(long units, int max_blocks, int& splits, int& bps) {
   const long pairs = units;
   int s = int((512 + pairs - 1) / pairs);
   int cap = (max_blocks + 31) / 32;
-  if (pairs * cap < 256) cap = (max_blocks + 7) / 8;
+  if (pairs * cap <= 64) cap = (max_blocks + 7) / 8;
   if (s > cap) s = cap;
   if (s < 1) s = 1;
   if (s < (max_blocks + kMaxSplitBlocks - 1) / kMaxSplitBlocks)
