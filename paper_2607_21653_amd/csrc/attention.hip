@@ -3,13 +3,14 @@
 // R = G*(1+k) query rows (G = Hq/Hkv query heads, 1+k positions) share every key/value
 // block, so each K/V byte is read once per (b, h) and reused by all R rows on MFMA.
 //
-// Work split: workgroup = (b, h, query tile, split of the key range), 8 wavefronts (one
-// 16-row tile each; those without rows only load). A query tile holds all R rows when
-// R <= 128 (the verify step); longer windows (prefill) are cut into tiles of floor(128 / G)
-// positions, each reading the keys its last position sees.
-// The number of splits is chosen so the grid holds ~512 workgroups (at B*Hkv*tiles >= 512
-// there is no split and no merge pass) and no split exceeds 2048 blocks. The wavefronts split the R query rows and
-// share every 32-key block pair through a double-buffered LDS ring (details at the kernel).
+// Work split: workgroup = (b, h, query tile, split of the key range). A query tile holds all R
+// rows when R <= 128 (the verify step); longer windows (prefill) are cut into tiles of
+// floor(128 / G) positions, each reading the keys its last position sees. Tiles of up to 64 rows
+// (attn_lds_kernel): 8 wavefronts in two key groups, one 16-row tile each; taller ones
+// (attn_rows_kernel): 4 wavefronts with up to two tiles each. The number of splits is chosen so the
+// grid holds ~512 workgroups (at B*Hkv*tiles >= 512 there is no split and no merge pass) and no
+// split exceeds 2048 blocks. The wavefronts share every 32-key block pair through an LDS ring
+// (details at the kernels).
 // Per pair, on v_mfma_f32_16x16x32_bf16:
 //   S^T[32 keys x 16 rows] = K Q^T   (A = K rows from LDS, B = Q^T held in registers)
 //   O^T[D x 16 rows]      += V^T P^T (A = V^T: the V cache stores a block as [D][16 tokens],
@@ -59,19 +60,14 @@ MOLT_DEV long out_index(const AttnParams& p, long t, long c, long cols, int esiz
 }
 
 // ---------------------------------------------------------------- MFMA kernel
-// Workgroup = (b, h, query tile, split), NW wavefronts that split the query rows (wavefront
-// w owns the 16-row tile w) and share every 32-key block pair through LDS: per pair the
-// 64 NW threads copy its K and V blocks (4 x 16 D bytes) with coalesced 16-byte loads,
-// kept kDepth pairs ahead in registers, into a double-buffered ring; one LDS-only barrier
-// per pair. Each wavefront keeps only its own rows' Q fragments and O accumulator; with 3
-// pairs in flight the 8-wavefront kernel takes 122 registers, so two workgroups (16
-// wavefronts, 6 pairs in flight) share a CU; no cross-wavefront merge at the end. The
-// kernel is bound by the latency of each wavefront's per-pair chain (counters: LDS active
-// ~25%, MFMA busy ~17% of cycles), so wavefronts per CU set its pace: at 72 rows and
-// context 2048 two row tiles per wavefront of 4 (334 registers, one wavefront per SIMD)
-// reached 36% of HBM bandwidth, one 8-wavefront workgroup per CU (6 pairs in flight)
-// 45%, two per CU 62%; at 40 rows two 4-wavefront workgroups per CU (6 pairs each) reached
-// 56-59% at contexts 4096-65536, two 8-wavefront ones 60-61%.
+// Workgroup = (b, h, query tile of up to 64 rows, split), two key groups of 4 wavefronts: group
+// g takes the block pairs g, g + 2, ... with its own running softmax, its wavefront w the 16-row
+// tile w. Per step the 512 threads copy two pairs' K and V blocks (2 x 4 x 16 D bytes) with
+// coalesced 16-byte loads, kept a step ahead in registers, into a double-buffered ring; one
+// LDS-only barrier per step; the groups are merged through LDS at the end. The kernel is bound by
+// the latency of each wavefront's per-pair chain (counters: LDS active ~30%, MFMA busy ~19% of
+// cycles), so wavefronts per CU and keys in flight set its pace: one key group of the same 8
+// wavefronts took 357 us against 340 in the full-depth step, 4-wavefront workgroups more.
 // Key order inside a pair for the MFMA k-index: lane group g (of 4) holds keys
 // 8 (g % 2) .. +7 of block g / 2. S^T MFMA t (t = 0, 1) computes rows m = 4 g + i for keys
 // 8 (g % 2) + 4 t + i of block g / 2, so the 8 scores of a lane are those 8 contiguous keys
@@ -115,8 +111,10 @@ MOLT_DEV void store_row(const AttnParams& p, int b, int h, int G, int r, int r0,
   }
 }
 
-template <int D, int NW, int KS>
-__global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void attn_lds_kernel(AttnParams p) {
+template <int D>
+__global__ __launch_bounds__(512, 2) void attn_lds_kernel(AttnParams p) {
+  constexpr int NW = 8;                 // wavefronts
+  constexpr int KS = 2;                 // key groups
   constexpr int kThreads = 64 * NW;
   constexpr int RTW = 1;                // 16-row tiles per wavefront
   constexpr int NRT = NW / KS;          // row tiles per key group
@@ -126,10 +124,9 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) void attn_lds_kernel(Attn
   constexpr int PAIR = 4 * KB;          // K0, K1, V0, V1
   constexpr int CPT = PAIR / 16 / kThreads;   // 16-byte chunks per thread per pair
   static_assert(CPT >= 1 && CPT * 16 * kThreads == PAIR, "chunks per thread");
-  // steps (KS pairs each) loaded ahead into registers: 8-wavefront workgroups hold 3 pairs
-  // with one key group, which keeps them at 122 registers, so two fit per CU; with two key
-  // groups one step (2 pairs) ahead
-  constexpr int kDepth = KS == 2 ? 1 : NW == 8 ? 3 : 6;
+  // steps (KS pairs each) loaded ahead into registers: with one, 119 registers, so that two
+  // workgroups fit per CU (two steps ahead at one per CU took the same time)
+  constexpr int kDepth = 1;
   __shared__ __attribute__((aligned(16))) uint8_t lds[2 * KS][PAIR];
 
   // Workgroup i runs on XCD i % 8. With the work item equal to i and 8 splits, XCD x would
@@ -836,7 +833,7 @@ hipError_t launch_d(const AttnParams& p, int B, int R, hipStream_t s) {
   const int Rt = (p.Hq / p.Hkv) * p.tq;     // rows of a query tile
   const long grid = long(B) * p.Hkv * p.qtiles * p.splits;
   // two key groups when a query tile's row tiles fit half the wavefronts
-  if ((Rt + 15) / 16 <= 4) attn_lds_kernel<D, 8, 2><<<grid, 512, 0, s>>>(p);
+  if ((Rt + 15) / 16 <= 4) attn_lds_kernel<D><<<grid, 512, 0, s>>>(p);
   else if (p.qtiles == 1) attn_rows_kernel<D, true><<<grid, kRowWaves * kWave, 0, s>>>(p);
   else attn_rows_kernel<D, false><<<grid, kRowWaves * kWave, 0, s>>>(p);
   if (p.splits > 1) attn_merge_kernel<D><<<B * p.Hkv * ((R + 1024 / D - 1) / (1024 / D)), 256, 0, s>>>(p);

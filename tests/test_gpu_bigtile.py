@@ -1,7 +1,7 @@
 """The big-tile GEMM (32 ab rows x 256 columns, ab = 2..5) at the edges of its tiles: one row
 more or less than whole tiles, a last column tile of fewer than 256 columns, fewer K slices
 than its pipeline is deep, accumulation; and its fused RoPE / cache-write epilogue against
-the LDS-tiled kernel's (windows of 64 rows run there): both add the products of a K range in
+the LDS-tiled kernel's (windows of 141 and 150 rows run there): both add the products of a K range in
 the same order, so the caches agree bit for bit."""
 import pytest
 import torch
@@ -34,11 +34,11 @@ def test_bigtile_gemm(molt_lib, M, N, K, acc):
     assert bool(((C - (A.double() @ B.double().T + c0)).abs() <= bound).all())
 
 
-@pytest.mark.parametrize("Hq,Hkv,n,ctx", [
-    (32, 4, 705, 37),        # 40 heads, ragged rows
-    (27, 9, 1500, 0),        # 45 heads: the last column tile holds one head
+@pytest.mark.parametrize("Hq,Hkv,n,ctx,small", [
+    (32, 4, 705, 37, 141),   # 40 heads, ragged rows
+    (27, 9, 1500, 0, 150),   # 45 heads: the last column tile holds one head
 ])
-def test_rope_epilogue_matches_small_windows(molt_lib, Hq, Hkv, n, ctx):
+def test_rope_epilogue_matches_small_windows(molt_lib, Hq, Hkv, n, ctx, small):
     print(f"case Hq={Hq} Hkv={Hkv} n={n} ctx={ctx}", flush=True)
     w = workloads.LAYER_BF16.scaled(name="bigtile_rope", batch=1, k=n - 1, d_model=512, n_q_heads=Hq,
                                     n_kv_heads=Hkv, n_experts=4, top_k=2, d_ff=128, ctx_lo=ctx, ctx_hi=ctx)
@@ -49,7 +49,7 @@ def test_rope_epilogue_matches_small_windows(molt_lib, Hq, Hkv, n, ctx):
     x = torch.randn(n, 512, generator=torch.Generator().manual_seed(4))
     bt = dev(torch.from_numpy(layout.block_tables))
     caches = []
-    for window in (n, 64):
+    for window in (n, small):
         kc, vc = (dev(c) for c in workloads.make_kv_cache(w, layout, 3, 0))
         rows = []
         for s in range(0, n, window):
