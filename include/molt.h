@@ -463,7 +463,7 @@ int molt_mtp_draft(const molt_model* target, const molt_mtp* mtp, const molt_kv*
  * launches beyond the pool are not timed. Process-wide state: enable, run and read
  * from one host thread.
  * Groups: 0 attention (+ split merge), 1 expert GEMMs (gate_up + down), 2 LM head,
- * 3 sampler (all four passes), 4 dense projections (QKV, O, router).
+ * 3 sampler (all its passes), 4 dense projections (QKV, O, router).
  * ---------------------------------------------------------------------------- */
 typedef enum {
   MOLT_PROF_ATTENTION = 0,
