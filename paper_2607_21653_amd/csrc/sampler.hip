@@ -141,7 +141,7 @@ constexpr double kExpInvL = 0x1.71547652b82fep+8;   // 256 / ln2
 constexpr double kExpLhi = 0x1.62e42fef80000p-9;    // ln2 / 256, 34 significant bits
 constexpr double kExpLlo = 0x1.1cf79abc9e3b4p-44;   // ln2 / 256 - kExpLhi
 constexpr double kExpRound = 0x1.8p+52;
-constexpr float kExpMin = -600.0f;
+constexpr double kExpMin = -600.0;
 
 MOLT_DEV double exp_nonpos(double x, const double* tab) {
   const double nr = fma(x, kExpInvL, kExpRound);
@@ -237,15 +237,16 @@ MOLT_DEV unsigned long long grid_floor(double r) {
   return (mant << 10) >> min(down, 63);              // mant << 10 < 2^63
 }
 
-// Logits below m - kMassMin have p < 2^-62, mass 0 whatever q is: they are raised to it (and so
-// are -inf and NaN), which keeps exp_nonpos in its range.
-constexpr float kMassMin = 64.0f;
+// Logits below m - 64 have p < 2^-62, mass 0 whatever q is: their difference (-inf and NaN too) is
+// raised to kMassMin, which keeps exp_nonpos in its range. The difference in f64 and not the logit in
+// f32, where m - 64 is m itself from |m| = 2^30 on and every logit would be raised to the largest.
+constexpr double kMassMin = -64.0;
 
 // residual mass of one logit on the 2^62 grid; tab is scaled by 1 / S, so that the exponential is
 // p_t (only S's rounding remains)
-MOLT_DEV unsigned long long grid_mass(float l, double m, float lmin, int mode, float qv, bool is_draft,
+MOLT_DEV unsigned long long grid_mass(float l, double m, int mode, float qv, bool is_draft,
                                       const double* tab) {
-  const double p = exp_nonpos(double(fmaxf(l, lmin)) - m, tab);
+  const double p = exp_nonpos(fmax(double(l) - m, kMassMin), tab);
   double r = p;
   if (mode == 1) r = p - double(qv);
   else if (mode == 2 && is_draft) r = p - 1.0;
@@ -281,15 +282,15 @@ MOLT_DEV void quad_load(const float* lrow, const float* qrow, int t0, int V, int
   }
 }
 
-// masses of a loaded quad (0 past V), and their sum
+// masses of a loaded quad (0 past V, and where the row's sum is not a number), and their sum
 MOLT_DEV unsigned long long quad_mass(const Quad& d, int t0, int V, const FinalDraw& f, int mode,
                                       const double* tab, unsigned long long (&g)[4]) {
   unsigned long long sum = 0;
-  const float lmin = float(f.m) - kMassMin;          // f.m is an f32 value
+  const int n = f.S > 0.0 ? V : 0;
   const int dr = f.draft - t0;                       // the draft's place in the quad, if any
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    g[e] = t0 + e < V ? grid_mass(d.l[e], f.m, lmin, mode, d.q[e], dr == e, tab) : 0ull;
+    g[e] = t0 + e < n ? grid_mass(d.l[e], f.m, mode, d.q[e], dr == e, tab) : 0ull;
     sum += g[e];
   }
   return sum;
@@ -644,10 +645,11 @@ __global__ __launch_bounds__(kThreads) void softmax_write_kernel(const float* __
     }
   }
   __syncthreads();
-  const double m = s_m;
-  exp_table_init(tab, s_inv, threadIdx.x, kThreads);
+  const double m = s_m, inv = s_inv;
+  exp_table_init(tab, 1.0, threadIdx.x, kThreads);
   __syncthreads();
-  const float lmin = float(m) + kExpMin;             // q = 0 in f32 long before
+  // 1 / S as a factor and not in the table: a sum that is not a number stays one in q
+  auto prob = [&](float l) { return float(exp_nonpos(fmax(double(l) - m, kExpMin), tab) * inv); };
   const float* src = logits + row * long(V) + long(c) * kChunk;
   float* dst = q + row * q_stride + long(c) * kChunk;
   const int n = min(kChunk, V - c * kChunk);
@@ -659,12 +661,12 @@ __global__ __launch_bounds__(kThreads) void softmax_write_kernel(const float* __
       const floatx4_t l = __builtin_nontemporal_load(reinterpret_cast<const floatx4_t*>(src + e0));
       floatx4_t o;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) o[e] = float(exp_nonpos(double(fmaxf(l[e], lmin)) - m, tab));
+      for (int e = 0; e < 4; ++e) o[e] = prob(l[e]);
       *reinterpret_cast<floatx4_t*>(dst + e0) = o;
     }
   } else {
     for (int e = threadIdx.x; e < n; e += kThreads)
-      dst[e] = float(exp_nonpos(double(fmaxf(src[e], lmin)) - m, tab));
+      dst[e] = prob(src[e]);
   }
 }
 
