@@ -44,6 +44,7 @@ constexpr int kRowsPerBatch = 16;              // accept rows examined per batch
 constexpr float kL2e = 0x1.715476p+0f;         // log2(e) rounded to f32
 constexpr float kL2eLo = 0x1.4ae0c0p-26f;      // log2(e) - kL2e
 constexpr float kLn2 = 0x1.62e430p-1f;         // ln 2
+constexpr float kSparse = 0x1p30f;             // logits this large: spacing 64 below, 128 above
 
 struct FinalDraw {
   double m;      // row max
@@ -91,7 +92,12 @@ __global__ __launch_bounds__(kThreads) void chunk_stats_kernel(const float* __re
   for (int i = 0; i < kPerThread; ++i) mx = fmaxf(mx, v[i]);
   mx = block_max<kThreads / kWave>(mx, redf);
   float s = 0.f;
-  if (mx != -INFINITY) {
+  if (fabsf(mx) >= kSparse && mx != INFINITY && mx != -INFINITY) {
+    // f32 logits of this size lie 64 and more apart: all but those equal to mx weigh under 2^-92
+    // (and mx - 200 below may round to mx)
+#pragma unroll
+    for (int i = 0; i < kPerThread; ++i) s += v[i] == mx ? 1.f : 0.f;
+  } else if (mx != -INFINITY) {
     // exp(l - mx) to ~1 ulp with every rounding compensated: logits below mx - 200 (and the
     // padding's -inf) are raised to it, where exp underflows to 0 in f32; d + err == l - mx
     // exactly (TwoSum); d log2(e) = t + terr (FMA split, log2(e) = kL2e + kL2eLo); then

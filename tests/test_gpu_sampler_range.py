@@ -53,3 +53,35 @@ def test_draw(lib, top, B, k, V, with_q):
         assert ok.mean() > 0.95
         assert (n == o["n_accepted"]).all()
         assert (toks[ok] == o["tokens"][ok]).all()
+
+
+@pytest.mark.parametrize("top", [1.0737e9, 4.2e9, 4.4e9, 1e10, 1e30, BIG, -4.4e9, -1e10, -1e30, -BIG])
+@pytest.mark.parametrize("B,k,V,with_q", [(3, 2, 20003, True), (2, 0, 1000, False), (200, 2, 8200, False),
+                                          (200, 1, 1001, True)])
+def test_row_sums(lib, top, B, k, V, with_q):
+    """Forced drafts and log-probs: the row's sum is the number of its largest logits."""
+    print(f"case top={top} B={B} k={k} V={V} q={with_q}", flush=True)
+    g = np.random.Generator(np.random.Philox(V + k))
+    for equal in (False, True):
+        logits, at = _rows(g, B, k + 1, V, top, equal)
+        if top == -BIG:          # the lowest float32 is the largest: beside it only -inf
+            logits = np.where(logits == -BIG, -np.inf, logits).astype(np.float32)
+            np.put_along_axis(logits, at[..., None], np.float32(top), 2)
+            if equal:
+                np.put_along_axis(logits, at[..., None] + 1, np.float32(top), 2)
+        drafts = at[:, :k].astype(np.int32)
+        drafts[::4] = (drafts[::4] + 7) % V
+        q = None
+        if with_q:
+            q = g.random((B, k, V), dtype=np.float32)
+            q /= q.sum(-1, keepdims=True)
+        u = g.random((B, k + 1), dtype=np.float32)
+        toks, n, lp = _run(lib, logits, drafts, u, q)
+        o = osamp.spec_accept(logits, drafts, u, q)
+        ok = o["draw_margin"] > 2e-8
+        if k:
+            ok &= np.nan_to_num(o["accept_margin"], nan=np.inf).min(1) > 1e-6
+        assert ok.mean() > 0.9
+        assert (n[ok] == o["n_accepted"][ok]).all()
+        assert (toks[ok] == o["tokens"][ok]).all()
+        np.testing.assert_allclose(lp[ok], o["logprobs"][ok], rtol=1e-6, atol=1e-6, equal_nan=True)
