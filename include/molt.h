@@ -289,7 +289,7 @@ int molt_decoder_forward(const molt_model* m, const molt_kv* kv, int B, int k, f
  * final RMSNorm, LM head to f32 logits, then molt_spec_accept's rule.
  *   tokens       [B, 1+k] i32: the last emitted token, then the k drafts (in [0, V))
  *   draft_probs, uniforms, out_tokens, out_num_accepted, out_logprobs: as in
- *                molt_spec_accept (drafts are tokens[:, 1:])
+ *                molt_spec_accept (drafts are tokens[:, 1:]); out_tokens may be `tokens`
  *   out_logits   [B, 1+k, V] f32, or NULL (then kept in the workspace)
  *   out_routes   [n_layers, B*(1+k), top_k] i32, or NULL
  *   out_hidden   [B*(1+k), d] f32 final residual stream (before the final norm), or

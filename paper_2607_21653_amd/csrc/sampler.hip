@@ -306,7 +306,7 @@ MOLT_DEV unsigned long long quad_mass(const Quad& d, int t0, int V, const FinalD
 // One workgroup per sequence: its accept decisions, batches of 16 rows (row r on wavefront
 // r % 4): row moments (m, S) from the chunk statistics, the tests u*q*S < exp(l_x - m) in
 // f64, n, and the descriptor of the final draw, which is returned. With `write` the accepted
-// drafts, their log-probs, n and the descriptor are stored too.
+// drafts (where out_tokens is given), their log-probs, n and the descriptor are stored too.
 MOLT_DEV FinalDraw decide(const float* __restrict__ logits, const float* __restrict__ q,
                           const int32_t* __restrict__ drafts, const float* __restrict__ u, int b,
                           int k, int V, int nch, const float* __restrict__ cmax,
@@ -417,7 +417,7 @@ MOLT_DEV FinalDraw decide(const float* __restrict__ logits, const float* __restr
           break;
         }
         if (!write) continue;
-        out_tokens[r0 + r] = s_x[i];
+        if (out_tokens) out_tokens[r0 + r] = s_x[i];
         if (out_lp) out_lp[r0 + r] = float((s_lx[i] - s_m[i]) - log(s_S[i]));
       }
     }
@@ -427,7 +427,7 @@ MOLT_DEV FinalDraw decide(const float* __restrict__ logits, const float* __restr
   if (!write) return s_fin;
   const int n = s_n;
   for (int j = n + 1 + int(threadIdx.x); j <= k; j += kThreads) {
-    out_tokens[r0 + j] = -1;
+    if (out_tokens) out_tokens[r0 + j] = -1;
     if (out_lp) out_lp[r0 + j] = __builtin_nanf("");
   }
   if (threadIdx.x == 0) {
@@ -452,8 +452,8 @@ __global__ __launch_bounds__(kThreads) void decide_kernel(
 // steps. The pass is bound by its ~30 instructions per logit and their latency, so it is cut small:
 // with all 8 steps in one workgroup a wavefront alone took 9.5 us (one sequence, vocabulary 151936;
 // with 2 steps 4.0), and 128 sequences ended 1 us later. kDecide: every workgroup takes its
-// sequence's decisions for itself instead of reading them (the first of them stores them), which
-// saves a launch where the chip is mostly empty anyway (one sequence: 4.8 + 4.0 us and the gap
+// sequence's decisions for itself instead of reading them (the first of them stores them, all but the
+// tokens: out_tokens may be the array that the others read the drafts from), which saves a launch where the chip is mostly empty anyway (one sequence: 4.8 + 4.0 us and the gap
 // between the launches against 7.9); with 128 sequences it costs 7 us.
 constexpr int kMassSteps = 2;
 constexpr int kMassParts = 8 / kMassSteps;
@@ -461,9 +461,8 @@ template <bool kVec, bool kDecide>
 __global__ __launch_bounds__(kThreads) void mass_kernel(
     const float* __restrict__ logits, const float* __restrict__ q, const int32_t* __restrict__ drafts,
     const float* __restrict__ u, int B, int k, int V, int nch, const float* __restrict__ cmax,
-    const double* __restrict__ csum, int dstride, int doff, int32_t* __restrict__ out_tokens,
-    int32_t* __restrict__ out_n, float* __restrict__ out_lp, FinalDraw* __restrict__ fin,
-    unsigned long long* __restrict__ sub_tot) {
+    const double* __restrict__ csum, int dstride, int doff, int32_t* __restrict__ out_n,
+    float* __restrict__ out_lp, FinalDraw* __restrict__ fin, unsigned long long* __restrict__ sub_tot) {
   __shared__ double s_tab[256];
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
   for (long id = blockIdx.x; id < long(B) * nch * kMassParts; id += gridDim.x) {
@@ -473,7 +472,7 @@ __global__ __launch_bounds__(kThreads) void mass_kernel(
     FinalDraw f;
     if constexpr (kDecide)
       f = decide(logits, q, drafts, u, b, k, V, nch, cmax, csum, dstride, doff, c == 0 && part == 0,
-                 out_tokens, out_n, out_lp, fin);
+                 nullptr, out_n, out_lp, fin);
     else f = fin[b];
     const float* lrow = logits + (r0 + f.row) * V;
     const float* qrow = f.mode == 1 ? q + (long(b) * k + f.row) * V : nullptr;
@@ -495,16 +494,21 @@ __global__ __launch_bounds__(kThreads) void mass_kernel(
 
 // ---- pass 4 ---------------------------------------------------------------------------
 // One wavefront per sequence. Zero residual mass (p <= q everywhere after rounding) falls
-// back to p: the chunk and sub-block masses of p are then recomputed here (rare path).
-template <bool kVec>
+// back to p: the chunk and sub-block masses of p are then recomputed here (rare path). kDecide: the
+// sequence's accepted drafts (k < 64) are stored here too, read and written by one instruction each, as
+// out_tokens may overlap them.
+template <bool kVec, bool kDecide>
 __global__ __launch_bounds__(kWave) void draw_pick_kernel(
-    const float* __restrict__ logits, const float* __restrict__ q, const float* __restrict__ u,
-    int k, int V, int nch, const FinalDraw* __restrict__ fin,
-    const unsigned long long* __restrict__ sub_tot, int32_t* __restrict__ out_tokens, float* __restrict__ out_lp) {
+    const float* __restrict__ logits, const float* __restrict__ q, const int32_t* drafts,
+    const float* __restrict__ u, int k, int V, int nch, int dstride, int doff,
+    const FinalDraw* __restrict__ fin, const unsigned long long* __restrict__ sub_tot, int32_t* out_tokens,
+    float* __restrict__ out_lp) {
   __shared__ double s_tab[256];
   const int b = blockIdx.x;
   const int lane = threadIdx.x;
   const FinalDraw f = fin[b];
+  int draft = -1;
+  if (kDecide && lane < f.row) draft = drafts[long(b) * dstride + doff + lane];
   exp_table_init(s_tab, 1.0 / f.S, lane, kWave);
   __syncthreads();
   const float* lrow = logits + (long(b) * (k + 1) + f.row) * V;
@@ -612,12 +616,14 @@ __global__ __launch_bounds__(kWave) void draw_pick_kernel(
       }
     }
   }
-  if (lane == 0) {
+  if (kDecide) {
+    if (lane <= k) out_tokens[long(b) * (k + 1) + lane] = lane == f.row ? token : draft;
+  } else if (lane == 0) {
     out_tokens[long(b) * (k + 1) + f.row] = token;
-    if (out_lp)
-      out_lp[long(b) * (k + 1) + f.row] =
-          token >= 0 ? float((double(lrow[token]) - f.m) - log(f.S)) : __builtin_nanf("");
   }
+  if (lane == 0 && out_lp)
+    out_lp[long(b) * (k + 1) + f.row] =
+        token >= 0 ? float((double(lrow[token]) - f.m) - log(f.S)) : __builtin_nanf("");
 }
 
 
@@ -775,14 +781,17 @@ hipError_t launch_spec_accept(const float* logits, const float* q, const int32_t
     chunk_stats_kernel<kVec><<<g1, kThreads, 0, s>>>(logits, rows, V, nch, cmax, csum);
     if (few) {
       mass_kernel<kVec, true><<<g2, kThreads, 0, s>>>(logits, q, drafts, u, B, k, V, nch, cmax, csum, ds,
-                                                      draft_offset, out_tokens, out_n, out_lp, fin, stot);
+                                                      draft_offset, out_n, out_lp, fin, stot);
+      draw_pick_kernel<kVec, true><<<g3, kWave, 0, s>>>(logits, q, drafts, u, k, V, nch, ds, draft_offset, fin,
+                                                        stot, out_tokens, out_lp);
     } else {
       decide_kernel<<<g3, kThreads, 0, s>>>(logits, q, drafts, u, k, V, nch, cmax, csum, ds,
                                             draft_offset, out_tokens, out_n, out_lp, fin);
       mass_kernel<kVec, false><<<g2, kThreads, 0, s>>>(logits, q, drafts, u, B, k, V, nch, cmax, csum, ds,
-                                                       draft_offset, out_tokens, out_n, out_lp, fin, stot);
+                                                       draft_offset, out_n, out_lp, fin, stot);
+      draw_pick_kernel<kVec, false><<<g3, kWave, 0, s>>>(logits, q, drafts, u, k, V, nch, ds, draft_offset, fin,
+                                                         stot, out_tokens, out_lp);
     }
-    draw_pick_kernel<kVec><<<g3, kWave, 0, s>>>(logits, q, u, k, V, nch, fin, stot, out_tokens, out_lp);
   };
   if (vec) run(std::true_type{});
   else run(std::false_type{});
