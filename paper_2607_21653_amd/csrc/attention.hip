@@ -746,7 +746,7 @@ __global__ __launch_bounds__(kF32AttnWaves * kWave) void attn_f32_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
   if (threadIdx.x < D) s_q[threadIdx.x] = q[(long(t) * p.Hq + hq) * D + threadIdx.x];
   __syncthreads();
-  float m = kNegBig, l = 0.f;
+  float m = -INFINITY, l = 0.f;                      // a finite start would be above the lowest scores
   float acc[DL];
 #pragma unroll
   for (int c = 0; c < DL; ++c) acc[c] = 0.f;
@@ -765,8 +765,8 @@ __global__ __launch_bounds__(kF32AttnWaves * kWave) void attn_f32_kernel(
       }
       s = ((d[0] + d[1]) + (d[2] + d[3])) * scale;
     }
-    const float mn = fmaxf(m, wave_max(s));          // finite: the chunk's first key is visible
-    const float alpha = expf(m - mn);
+    const float mn = fmaxf(m, wave_max(s));
+    const float alpha = m == -INFINITY ? 0.f : expf(m - mn);
     const float pe = s == -INFINITY ? 0.f : expf(s - mn);
     l = l * alpha + wave_sum(pe);
     m = mn;
@@ -801,7 +801,7 @@ __global__ __launch_bounds__(kF32AttnWaves * kWave) void attn_f32_kernel(
     float lt = 0.f, o = 0.f;
 #pragma unroll
     for (int w = 0; w < kF32AttnWaves; ++w) {
-      const float f = expf(s_m[w] - mm);             // wavefronts without keys: exactly 0 * 0
+      const float f = s_m[w] == -INFINITY ? 0.f : expf(s_m[w] - mm);   // -inf: a wavefront without keys
       lt += s_l[w] * f;
       o += s_o[w][threadIdx.x] * f;
     }

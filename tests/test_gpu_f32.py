@@ -70,3 +70,30 @@ def test_f32_attention(molt_lib, D, k, lo, hi):
     out = molt_lib.paged_attention(dev(q), dev(kc), dev(vc), dev(torch.from_numpy(layout.block_tables)),
                                    dev(torch.from_numpy(layout.context_lens)), k)
     assert max_abs(out.cpu().numpy(), ref.reshape(B * (k + 1), -1)) <= 1e-5
+
+
+@pytest.mark.parametrize("lo,hi", [(0, 0), (70, 70), (300, 300)])
+def test_f32_attention_scores_of_any_size(molt_lib, lo, hi):
+    """Finite scores far below -1e30 (queries and keys of 1e17): the softmax depends on their
+    differences only. Each query of -1e17 e_0 meets keys of first component 1e17 + small, so that
+    scores are about -1e33 and one key's is the largest by far: the output is that key's value."""
+    print(f"case ctx=[{lo},{hi}]", flush=True)
+    B, k, Hq, Hkv, D = 2, 1, 2, 1, 64
+    w = workloads.LAYER_BF16.scaled(batch=B, k=k, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=D, ctx_lo=lo,
+                                    ctx_hi=hi, dtype="f32")
+    layout = workloads.make_kv_layout(w, 6)
+    kc, vc = workloads.make_kv_cache(w, layout, 6, 0)
+    kc[:] = 0
+    kc[..., 0] = 1e17
+    best = {}
+    for b in range(B):
+        p = (lo + 1) // 2 if lo else 0
+        blk = int(layout.block_tables[b, p // 16])
+        kc[blk, 0, p % 16, 0] = 0.9e17
+        best[b] = vc[blk, 0, :, p % 16]
+    q = torch.zeros(B * (k + 1), Hq, D)
+    q[..., 0] = -1e17
+    out = molt_lib.paged_attention(dev(q), dev(kc), dev(vc), dev(torch.from_numpy(layout.block_tables)),
+                                   dev(torch.from_numpy(layout.context_lens)), k).cpu().view(B, k + 1, Hq, D)
+    for b in range(B):
+        assert bool((out[b] == best[b]).all())
