@@ -208,6 +208,11 @@ int molt_pack_weights(const void* src, void* dst, long long rows, long long row_
  *   out           [T, Hq*D]   dtype
  * Supported: dtype F32 or BF16, D in {64, 128}, Hq % Hkv == 0, Hq/Hkv*(1+k) <= 128.
  * context_lens[b] + k + 1 <= 16 * max_blocks_per_seq is the caller's duty.
+ * Workspace: partial results of splits of the key range. For few sequences of short tables the
+ * size includes finer splits, which a larger batch or longer tables do not need; a smaller
+ * workspace that holds the splits of at least 32 blocks each is accepted too and used with
+ * those (0 bytes, or NULL, for tables of up to 32 blocks). The same holds for every call with
+ * attention below.
  * ---------------------------------------------------------------------------- */
 size_t molt_paged_attention_workspace_size(int B, int k, int n_q_heads, int n_kv_heads,
                                            int head_dim, int max_blocks_per_seq);

@@ -14,6 +14,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libmolt.so")
 
 MOLT_F32, MOLT_BF16, MOLT_FP8_E4M3 = 0, 1, 2
+MOLT_ERR_WORKSPACE = -3
 NOALLOC_SCRATCH_BYTES = 8 << 20   # MOLT_NOALLOC_SCRATCH_BYTES of include/molt.h
 DTYPE_CODE = {torch.float32: MOLT_F32, torch.bfloat16: MOLT_BF16, torch.uint8: MOLT_FP8_E4M3}
 NAME_CODE = {"f32": MOLT_F32, "bf16": MOLT_BF16, "fp8": MOLT_FP8_E4M3}
@@ -157,6 +158,17 @@ def _workspace(nbytes, device, ws=None):
         return ws, ws.numel()
     t = torch.empty(nbytes, dtype=torch.uint8, device=device)
     return t, nbytes
+
+
+def _call(name, call, nbytes, device, ws):
+    """call(workspace address, its bytes) with the caller's workspace, also a smaller one where the
+    library takes it (coarser attention splits), else with one of nbytes."""
+    if ws is not None and ws.numel() < nbytes:
+        status = call(_ptr(ws), ws.numel())
+        if status != MOLT_ERR_WORKSPACE:
+            return _check(status, name)
+    t, nb = _workspace(nbytes, device, ws)
+    _check(call(_ptr(t), nb), name)
 
 
 # ------------------------------------------------------------------ spec accept
@@ -316,11 +328,14 @@ def paged_attention(q, k_cache, v_cache, block_tables, context_lens, k, workspac
     _dev(context_lens, torch.int32, (B,), "context_lens")
     maxb = block_tables.shape[1]
     out = torch.empty(T, Hq * D, dtype=q.dtype, device=q.device)
-    ws, nb = _workspace(lib.molt_paged_attention_workspace_size(B, k, Hq, Hkv, D, maxb), q.device, workspace)
-    st = lib.molt_paged_attention(_ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(block_tables),
-                                  _ptr(context_lens), B, k, Hq, Hkv, D, maxb, DTYPE_CODE[q.dtype],
-                                  _ptr(out), _ptr(ws), nb, _stream())
-    _check(st, "molt_paged_attention")
+
+    def call(ws, nb):
+        return lib.molt_paged_attention(_ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(block_tables),
+                                        _ptr(context_lens), B, k, Hq, Hkv, D, maxb, DTYPE_CODE[q.dtype],
+                                        _ptr(out), ws, nb, _stream())
+
+    _call("molt_paged_attention", call, lib.molt_paged_attention_workspace_size(B, k, Hq, Hkv, D, maxb),
+          q.device, workspace)
     return out
 
 
@@ -405,10 +420,13 @@ def decoder_forward(model, kv, B, k, x, want_routes=False, workspace=None):
     if want_routes:
         routes = torch.empty(model.struct.n_layers, B * (k + 1), model.struct.top_k,
                              dtype=torch.int32, device=x.device)
-    ws, nb = _workspace(decoder_workspace_size(model, B, k, kv.struct.max_blocks_per_seq), x.device, workspace)
-    st = lib.molt_decoder_forward(ctypes.byref(model.struct), ctypes.byref(kv.struct), B, k, _ptr(x),
-                                  _ptr(routes), _ptr(ws), nb, _stream())
-    _check(st, "molt_decoder_forward")
+
+    def call(ws, nb):
+        return lib.molt_decoder_forward(ctypes.byref(model.struct), ctypes.byref(kv.struct), B, k, _ptr(x),
+                                        _ptr(routes), ws, nb, _stream())
+
+    _call("molt_decoder_forward", call, decoder_workspace_size(model, B, k, kv.struct.max_blocks_per_seq),
+          x.device, workspace)
     return routes
 
 
@@ -439,13 +457,15 @@ def verify_step(model, kv, tokens, uniforms, draft_probs=None, want_logits=True,
                                         dtype=torch.int32, device=dev)
         if want_hidden:
             out["hidden"] = torch.empty(B * kp1, model.struct.d_model, dtype=torch.float32, device=dev)
-    ws, nb = _workspace(verify_step_workspace_size(model, B, k, kv.struct.max_blocks_per_seq), dev, workspace)
-    st = lib.molt_verify_step(ctypes.byref(model.struct), ctypes.byref(kv.struct), B, k, _ptr(tokens),
-                              _ptr(draft_probs), _ptr(uniforms), _ptr(out.get("logits")),
-                              _ptr(out["tokens"]), _ptr(out["n_accepted"]), _ptr(out["logprobs"]),
-                              _ptr(out.get("routes")), _ptr(out.get("hidden")), _ptr(ws), nb,
-                              _stream())
-    _check(st, "molt_verify_step")
+
+    def call(ws, nb):
+        return lib.molt_verify_step(ctypes.byref(model.struct), ctypes.byref(kv.struct), B, k, _ptr(tokens),
+                                    _ptr(draft_probs), _ptr(uniforms), _ptr(out.get("logits")),
+                                    _ptr(out["tokens"]), _ptr(out["n_accepted"]), _ptr(out["logprobs"]),
+                                    _ptr(out.get("routes")), _ptr(out.get("hidden")), ws, nb, _stream())
+
+    _call("molt_verify_step", call, verify_step_workspace_size(model, B, k, kv.struct.max_blocks_per_seq),
+          dev, workspace)
     return out
 
 
@@ -467,11 +487,14 @@ def prefill(model, kv, tokens, lens, want_hidden=False, want_routes=False, works
         out["hidden"] = torch.empty(B * n, m.d_model, dtype=torch.float32, device=dev)
     if want_routes:
         out["routes"] = torch.empty(m.n_layers, B * n, m.top_k, dtype=torch.int32, device=dev)
-    ws, nb = _workspace(prefill_workspace_size(model, B, n, kv.struct.max_blocks_per_seq), dev, workspace)
-    st = lib.molt_prefill(ctypes.byref(m), ctypes.byref(kv.struct), B, n, _ptr(tokens), _ptr(lens),
-                          _ptr(out["logits"]), _ptr(out.get("hidden")), _ptr(out.get("routes")),
-                          _ptr(ws), nb, _stream())
-    _check(st, "molt_prefill")
+
+    def call(ws, nb):
+        return lib.molt_prefill(ctypes.byref(m), ctypes.byref(kv.struct), B, n, _ptr(tokens), _ptr(lens),
+                                _ptr(out["logits"]), _ptr(out.get("hidden")), _ptr(out.get("routes")),
+                                ws, nb, _stream())
+
+    _call("molt_prefill", call, prefill_workspace_size(model, B, n, kv.struct.max_blocks_per_seq),
+          dev, workspace)
     return out
 
 
@@ -548,13 +571,14 @@ def score_tokens(model, kv, tokens, targets, replay_routes=None, want_logits=Fal
         out["logits"] = torch.empty(B, kp1, m.vocab, dtype=torch.float32, device=dev)
     if want_routes:
         out["routes"] = torch.empty(m.n_layers, B * kp1, m.top_k, dtype=torch.int32, device=dev)
-    ws, nb = _workspace(score_tokens_workspace_size(model, B, k, kv.struct.max_blocks_per_seq), dev,
-                        workspace)
-    st = lib.molt_score_tokens(ctypes.byref(m), ctypes.byref(kv.struct), B, k, _ptr(tokens),
-                               _ptr(targets), _ptr(replay_routes), _ptr(out["logprobs"]),
-                               _ptr(out.get("logits")), _ptr(out.get("routes")), _ptr(ws), nb,
-                               _stream())
-    _check(st, "molt_score_tokens")
+
+    def call(ws, nb):
+        return lib.molt_score_tokens(ctypes.byref(m), ctypes.byref(kv.struct), B, k, _ptr(tokens),
+                                     _ptr(targets), _ptr(replay_routes), _ptr(out["logprobs"]),
+                                     _ptr(out.get("logits")), _ptr(out.get("routes")), ws, nb, _stream())
+
+    _call("molt_score_tokens", call, score_tokens_workspace_size(model, B, k, kv.struct.max_blocks_per_seq),
+          dev, workspace)
     return out
 
 
@@ -602,14 +626,16 @@ def mtp_draft(target, mtp, kv, hidden, tokens, n_accepted, next_tokens, uniforms
     if out is None:
         out = {"drafts": torch.empty(B, k, dtype=torch.int32, device=dev),
                "draft_probs": None if greedy else torch.empty(B, k, V, dtype=torch.float32, device=dev)}
-    ws, nb = _workspace(mtp_draft_workspace_size(target, mtp, B, k, kv.struct.max_blocks_per_seq, W), dev,
-                        workspace)
-    st = lib.molt_mtp_draft_window(ctypes.byref(target.struct), ctypes.byref(mtp.struct),
-                                   ctypes.byref(kv.struct), B, W, k, _ptr(hidden), _ptr(tokens),
-                                   _ptr(n_accepted), _ptr(next_tokens),
-                                   _ptr(None if greedy else uniforms), _ptr(out["drafts"]),
-                                   _ptr(out["draft_probs"]), _ptr(ws), nb, _stream())
-    _check(st, "molt_mtp_draft")
+
+    def call(ws, nb):
+        return lib.molt_mtp_draft_window(ctypes.byref(target.struct), ctypes.byref(mtp.struct),
+                                         ctypes.byref(kv.struct), B, W, k, _ptr(hidden), _ptr(tokens),
+                                         _ptr(n_accepted), _ptr(next_tokens),
+                                         _ptr(None if greedy else uniforms), _ptr(out["drafts"]),
+                                         _ptr(out["draft_probs"]), ws, nb, _stream())
+
+    _call("molt_mtp_draft", call, mtp_draft_workspace_size(target, mtp, B, k, kv.struct.max_blocks_per_seq, W),
+          dev, workspace)
     return out
 
 

@@ -75,6 +75,22 @@ int check_ws(void* ws, size_t have, size_t need) {
   return MOLT_OK;
 }
 
+// Workspace of a carve_* function with these arguments (256 bytes for an unaligned start)
+template <typename Carve, typename... Args>
+size_t carved_bytes(Carve carve, Args... args) {
+  molt::Carver c(nullptr, 0);
+  carve(c, args...);
+  return c.used + 256;
+}
+
+// Calls with attention: `fine` is true where the workspace holds the finer attention splits (need(true),
+// the size that the size functions give), false where it holds the coarse ones (need(false)).
+template <typename Need>
+int check_attn_ws(void* ws, size_t have, Need need, bool& fine) {
+  fine = ws != nullptr && have >= need(true);
+  return fine ? MOLT_OK : check_ws(ws, have, need(false));
+}
+
 }  // namespace
 
 extern "C" {
@@ -466,7 +482,7 @@ static int attn_shape_ok(int B, int k, int Hq, int Hkv, int D, int max_blocks, m
 
 size_t molt_paged_attention_workspace_size(int B, int k, int Hq, int Hkv, int D, int max_blocks) {
   if (B < 1 || k < 0 || Hq < 1 || Hkv < 1 || D < 1 || max_blocks < 1) return 0;
-  return molt::attention_ws_bytes(B, k, Hq, Hkv, D, max_blocks);
+  return molt::attention_ws_bytes(B, k, Hq, Hkv, D, max_blocks, true);
 }
 
 int molt_paged_attention(const void* q, const void* k_cache, const void* v_cache,
@@ -475,13 +491,16 @@ int molt_paged_attention(const void* q, const void* k_cache, const void* v_cache
                          void* workspace, size_t workspace_bytes, molt_stream_t stream) {
   if (int r = attn_shape_ok(B, k, Hq, Hkv, D, max_blocks, dtype)) return r;
   REQUIRE(q && k_cache && v_cache && block_tables && context_lens && out, "a required pointer is NULL");
-  const size_t need = molt_paged_attention_workspace_size(B, k, Hq, Hkv, D, max_blocks);
-  if (int r = check_ws(workspace, workspace_bytes, dtype == MOLT_F32 ? 0 : need)) return r;
+  auto need = [&](bool f) {
+    return dtype == MOLT_F32 ? 0 : molt::attention_ws_bytes(B, k, Hq, Hkv, D, max_blocks, f);
+  };
+  bool fine = false;
+  if (int r = check_attn_ws(workspace, workspace_bytes, need, fine)) return r;
   hipError_t e;
   {
     ProfScope ps(MOLT_PROF_ATTENTION, reinterpret_cast<hipStream_t>(stream));
     e = molt::launch_paged_attention(q, k_cache, v_cache, block_tables, context_lens, B, k, Hq, Hkv,
-                                     D, max_blocks, dtype, out, false, workspace,
+                                     D, max_blocks, dtype, out, false, workspace, fine,
                                      reinterpret_cast<hipStream_t>(stream));
   }
   return hip_status(e, "molt_paged_attention");
@@ -533,10 +552,12 @@ struct DecWs {
   float* part; long part_elems;   // split-K partial sums of the QKV and O projections
   void* rope;                     // RoPE cos/sin of the step's positions, [T, D/2] f64 pairs
   int32_t* kv_slot;               // KV-cache slot of each token of the step (or -1)
+  bool fine;                      // attn_ws holds the finer attention splits
 };
 
-DecWs carve_dec(molt::Carver& c, const molt_model* m, int B, int k, int max_blocks) {
+DecWs carve_dec(molt::Carver& c, const molt_model* m, int B, int k, int max_blocks, bool fine) {
   DecWs w{};
+  w.fine = fine;
   const long T = long(B) * (k + 1);
   const int d = m->d_model, D = m->head_dim, Hq = m->n_q_heads, Hkv = m->n_kv_heads;
   const size_t es = dt_size(m->dtype);
@@ -551,7 +572,7 @@ DecWs carve_dec(molt::Carver& c, const molt_model* m, int B, int k, int max_bloc
     w.qkv = c.take<float>(T * (Hq + 2 * Hkv) * D);
   w.q = c.take<uint8_t>(T * Hq * D * es);
   w.attn = c.take<uint8_t>(Tp * Hq * D * es);
-  const size_t aws = m->dtype == MOLT_F32 ? 0 : molt::attention_ws_bytes(B, k, Hq, Hkv, D, max_blocks);
+  const size_t aws = m->dtype == MOLT_F32 ? 0 : molt::attention_ws_bytes(B, k, Hq, Hkv, D, max_blocks, fine);
   w.attn_ws = c.take<uint8_t>(aws);
   w.moe = carve_moe(c, int(T), d, m->n_experts, m->top_k, m->d_ff, m->dtype, m->expert_dtype);
   const long pq = gemm_part_elems(int(T), (Hq + 2 * Hkv) * D, d, m->dtype);
@@ -599,7 +620,7 @@ hipError_t run_decoder(const DecWs& w, const molt_model* m, const molt_kv* kv, i
       ProfScope ps(MOLT_PROF_ATTENTION, s);
       RUN(molt::launch_paged_attention(w.q, kv->k_cache[l], kv->v_cache[l], kv->block_tables,
                                        kv->context_lens, B, k, Hq, Hkv, D, kv->max_blocks_per_seq,
-                                       m->dtype, w.attn, true, w.attn_ws, s));
+                                       m->dtype, w.attn, true, w.attn_ws, w.fine, s));
     }
     int np = 1;   // O projection: accumulate into x, or leave split-K partials
     {
@@ -633,9 +654,7 @@ hipError_t run_decoder(const DecWs& w, const molt_model* m, const molt_kv* kv, i
 
 size_t molt_decoder_workspace_size(const molt_model* m, int B, int k, int max_blocks) {
   if (!m || B < 1 || k < 0 || max_blocks < 1 || !pair_ok(m->dtype, m->expert_dtype)) return 0;
-  molt::Carver c(nullptr, 0);
-  carve_dec(c, m, B, k, max_blocks);
-  return c.used + 256;
+  return carved_bytes(carve_dec, m, B, k, max_blocks, true);
 }
 
 int molt_decoder_forward(const molt_model* m, const molt_kv* kv, int B, int k, float* x,
@@ -643,11 +662,11 @@ int molt_decoder_forward(const molt_model* m, const molt_kv* kv, int B, int k, f
                          molt_stream_t stream) {
   if (int r = model_ok(m, kv, B, k, false)) return r;
   REQUIRE(x, "x is NULL");
-  if (int r = check_ws(workspace, workspace_bytes,
-                       molt_decoder_workspace_size(m, B, k, kv->max_blocks_per_seq)))
-    return r;
+  auto need = [&](bool f) { return carved_bytes(carve_dec, m, B, k, kv->max_blocks_per_seq, f); };
+  bool fine = false;
+  if (int r = check_attn_ws(workspace, workspace_bytes, need, fine)) return r;
   molt::Carver c(workspace, workspace_bytes);
-  DecWs w = carve_dec(c, m, B, k, kv->max_blocks_per_seq);
+  DecWs w = carve_dec(c, m, B, k, kv->max_blocks_per_seq, fine);
   return hip_status(run_decoder(w, m, kv, B, k, x, out_routes, nullptr, nullptr,
                                 reinterpret_cast<hipStream_t>(stream)),
                     "molt_decoder_forward");
@@ -655,14 +674,14 @@ int molt_decoder_forward(const molt_model* m, const molt_kv* kv, int B, int k, f
 
 namespace {
 struct StepWs { float* x; void* yf; float* logits; void* samp; DecWs dec; };
-StepWs carve_step(molt::Carver& c, const molt_model* m, int B, int k, int max_blocks, bool own_logits) {
+StepWs carve_step(molt::Carver& c, const molt_model* m, int B, int k, int max_blocks, bool fine) {
   StepWs w{};
   const long T = long(B) * (k + 1);
   w.x = c.take<float>(T * m->d_model);
   w.yf = c.take<uint8_t>(pad32(T) * m->d_model * dt_size(m->dtype));
-  w.logits = own_logits ? c.take<float>(T * long(m->vocab)) : nullptr;
+  w.logits = c.take<float>(T * long(m->vocab));
   w.samp = c.take<uint8_t>(molt::sampler_ws_bytes(B, k, m->vocab));
-  w.dec = carve_dec(c, m, B, k, max_blocks);
+  w.dec = carve_dec(c, m, B, k, max_blocks, fine);
   return w;
 }
 }  // namespace
@@ -670,9 +689,7 @@ StepWs carve_step(molt::Carver& c, const molt_model* m, int B, int k, int max_bl
 size_t molt_verify_step_workspace_size(const molt_model* m, int B, int k, int max_blocks) {
   if (!m || B < 1 || k < 0 || max_blocks < 1 || m->vocab < 1 || !pair_ok(m->dtype, m->expert_dtype))
     return 0;
-  molt::Carver c(nullptr, 0);
-  carve_step(c, m, B, k, max_blocks, true);
-  return c.used + 256;
+  return carved_bytes(carve_step, m, B, k, max_blocks, true);
 }
 
 int molt_verify_step(const molt_model* m, const molt_kv* kv, int B, int k, const int32_t* tokens,
@@ -683,12 +700,12 @@ int molt_verify_step(const molt_model* m, const molt_kv* kv, int B, int k, const
   if (int r = model_ok(m, kv, B, k, true)) return r;
   if (int r = spec_accept_shape_ok(B, k, m->vocab)) return r;
   REQUIRE(tokens && uniforms && out_tokens && out_num_accepted, "a required pointer is NULL");
-  if (int r = check_ws(workspace, workspace_bytes,
-                       molt_verify_step_workspace_size(m, B, k, kv->max_blocks_per_seq)))
-    return r;
+  auto need = [&](bool f) { return carved_bytes(carve_step, m, B, k, kv->max_blocks_per_seq, f); };
+  bool fine = false;
+  if (int r = check_attn_ws(workspace, workspace_bytes, need, fine)) return r;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   molt::Carver c(workspace, workspace_bytes);
-  StepWs w = carve_step(c, m, B, k, kv->max_blocks_per_seq, true);
+  StepWs w = carve_step(c, m, B, k, kv->max_blocks_per_seq, fine);
   float* logits = out_logits ? out_logits : w.logits;
   float* x = out_hidden ? out_hidden : w.x;   // the residual stream
   const int T = B * (k + 1);
@@ -712,16 +729,15 @@ int molt_verify_step(const molt_model* m, const molt_kv* kv, int B, int k, const
 
 namespace {
 struct PrefillWs { float* x; void* yf; float* hsel; void* ysel; DecWs dec; };
-PrefillWs carve_prefill(molt::Carver& c, const molt_model* m, int B, int n, int max_blocks,
-                        bool own_x) {
+PrefillWs carve_prefill(molt::Carver& c, const molt_model* m, int B, int n, int max_blocks, bool fine) {
   PrefillWs w{};
   const long T = long(B) * n;
   const size_t es = dt_size(m->dtype);
-  w.x = own_x ? c.take<float>(T * m->d_model) : nullptr;
+  w.x = c.take<float>(T * m->d_model);
   w.yf = c.take<uint8_t>(pad32(T) * m->d_model * es);
   w.hsel = c.take<float>(long(B) * m->d_model);
   w.ysel = c.take<uint8_t>(pad32(B) * m->d_model * es);
-  w.dec = carve_dec(c, m, B, n - 1, max_blocks);
+  w.dec = carve_dec(c, m, B, n - 1, max_blocks, fine);
   return w;
 }
 }  // namespace
@@ -729,9 +745,7 @@ PrefillWs carve_prefill(molt::Carver& c, const molt_model* m, int B, int n, int 
 size_t molt_prefill_workspace_size(const molt_model* m, int B, int n, int max_blocks) {
   if (!m || B < 1 || n < 1 || max_blocks < 1 || m->vocab < 1 || !pair_ok(m->dtype, m->expert_dtype))
     return 0;
-  molt::Carver c(nullptr, 0);
-  carve_prefill(c, m, B, n, max_blocks, true);
-  return c.used + 256;
+  return carved_bytes(carve_prefill, m, B, n, max_blocks, true);
 }
 
 int molt_prefill(const molt_model* m, const molt_kv* kv, int B, int n, const int32_t* tokens,
@@ -740,12 +754,12 @@ int molt_prefill(const molt_model* m, const molt_kv* kv, int B, int n, const int
   REQUIRE(n >= 1, "n = %d must be >= 1", n);
   if (int r = model_ok(m, kv, B, n - 1, true)) return r;
   REQUIRE(tokens && lens && out_logits, "a required pointer is NULL");
-  if (int r = check_ws(workspace, workspace_bytes,
-                       molt_prefill_workspace_size(m, B, n, kv->max_blocks_per_seq)))
-    return r;
+  auto need = [&](bool f) { return carved_bytes(carve_prefill, m, B, n, kv->max_blocks_per_seq, f); };
+  bool fine = false;
+  if (int r = check_attn_ws(workspace, workspace_bytes, need, fine)) return r;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   molt::Carver c(workspace, workspace_bytes);
-  PrefillWs w = carve_prefill(c, m, B, n, kv->max_blocks_per_seq, true);
+  PrefillWs w = carve_prefill(c, m, B, n, kv->max_blocks_per_seq, fine);
   float* x = out_hidden ? out_hidden : w.x;
   const int T = B * n;
   hipError_t e = molt::launch_embed(m->embed, tokens, T, m->d_model, m->vocab, m->dtype, x, s);
@@ -764,14 +778,14 @@ int molt_prefill(const molt_model* m, const molt_kv* kv, int B, int n, const int
 
 namespace {
 struct ScoreWs { float* x; void* yf; float* logits; void* lp; DecWs dec; };
-ScoreWs carve_score(molt::Carver& c, const molt_model* m, int B, int k, int max_blocks) {
+ScoreWs carve_score(molt::Carver& c, const molt_model* m, int B, int k, int max_blocks, bool fine) {
   ScoreWs w{};
   const long T = long(B) * (k + 1);
   w.x = c.take<float>(T * m->d_model);
   w.yf = c.take<uint8_t>(pad32(T) * m->d_model * dt_size(m->dtype));
   w.logits = c.take<float>(T * long(m->vocab));
   w.lp = c.take<uint8_t>(molt::token_logprob_ws_bytes(T, m->vocab));
-  w.dec = carve_dec(c, m, B, k, max_blocks);
+  w.dec = carve_dec(c, m, B, k, max_blocks, fine);
   return w;
 }
 }  // namespace
@@ -779,9 +793,7 @@ ScoreWs carve_score(molt::Carver& c, const molt_model* m, int B, int k, int max_
 size_t molt_score_tokens_workspace_size(const molt_model* m, int B, int k, int max_blocks) {
   if (!m || B < 1 || k < 0 || max_blocks < 1 || m->vocab < 1 || !pair_ok(m->dtype, m->expert_dtype))
     return 0;
-  molt::Carver c(nullptr, 0);
-  carve_score(c, m, B, k, max_blocks);
-  return c.used + 256;
+  return carved_bytes(carve_score, m, B, k, max_blocks, true);
 }
 
 int molt_score_tokens(const molt_model* m, const molt_kv* kv, int B, int k, const int32_t* tokens,
@@ -791,12 +803,12 @@ int molt_score_tokens(const molt_model* m, const molt_kv* kv, int B, int k, cons
   if (int r = model_ok(m, kv, B, k, true)) return r;
   if (int r = spec_accept_shape_ok(B, k, m->vocab)) return r;
   REQUIRE(tokens && targets && out_logprobs, "a required pointer is NULL");
-  if (int r = check_ws(workspace, workspace_bytes,
-                       molt_score_tokens_workspace_size(m, B, k, kv->max_blocks_per_seq)))
-    return r;
+  auto need = [&](bool f) { return carved_bytes(carve_score, m, B, k, kv->max_blocks_per_seq, f); };
+  bool fine = false;
+  if (int r = check_attn_ws(workspace, workspace_bytes, need, fine)) return r;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   molt::Carver c(workspace, workspace_bytes);
-  ScoreWs w = carve_score(c, m, B, k, kv->max_blocks_per_seq);
+  ScoreWs w = carve_score(c, m, B, k, kv->max_blocks_per_seq, fine);
   float* logits = out_logits ? out_logits : w.logits;
   const int T = B * (k + 1);
   hipError_t e = molt::launch_embed(m->embed, tokens, T, m->d_model, m->vocab, m->dtype, w.x, s);
@@ -826,7 +838,7 @@ struct MtpWs {
 };
 
 MtpWs carve_mtp(molt::Carver& c, const molt_model* t, const molt_model* L, int B, int W,
-                int max_blocks) {
+                int max_blocks, bool fine) {
   MtpWs w{};
   const long T = long(B) * W;
   const int d = t->d_model;
@@ -844,8 +856,8 @@ MtpWs carve_mtp(molt::Carver& c, const molt_model* t, const molt_model* L, int B
   w.ysel = c.take<uint8_t>(pad32(B) * d * es);
   w.logits = c.take<float>(long(B) * t->vocab);
   w.draw = c.take<uint8_t>(molt::draft_draw_ws_bytes(B, t->vocab));
-  w.cat = carve_dec(c, L, B, W - 1, max_blocks);
-  w.one = carve_dec(c, L, B, 0, max_blocks);
+  w.cat = carve_dec(c, L, B, W - 1, max_blocks, fine);
+  w.one = carve_dec(c, L, B, 0, max_blocks, fine);
   return w;
 }
 
@@ -875,9 +887,7 @@ size_t molt_mtp_draft_window_workspace_size(const molt_model* target, const molt
   if (!target || !mtp || !mtp->layer || B < 1 || window < 1 || k < 1 || max_blocks < 1 ||
       target->vocab < 1 || !pair_ok(mtp->layer->dtype, mtp->layer->expert_dtype))
     return 0;
-  molt::Carver c(nullptr, 0);
-  carve_mtp(c, target, mtp->layer, B, window, max_blocks);
-  return c.used + 256;
+  return carved_bytes(carve_mtp, target, mtp->layer, B, window, max_blocks, true);
 }
 
 size_t molt_mtp_draft_workspace_size(const molt_model* target, const molt_mtp* mtp, int B, int k,
@@ -894,13 +904,14 @@ int molt_mtp_draft_window(const molt_model* target, const molt_mtp* mtp, const m
   if (int r = mtp_ok(target, mtp, mtp_kv, B, W, k)) return r;
   REQUIRE(hidden && tokens && n_accepted && next_tokens && out_drafts, "a required pointer is NULL");
   REQUIRE(out_draft_probs == nullptr || uniforms, "sampled drafts (out_draft_probs) need uniforms");
-  if (int r = check_ws(workspace, workspace_bytes,
-                       molt_mtp_draft_window_workspace_size(target, mtp, B, W, k,
-                                                            mtp_kv->max_blocks_per_seq)))
-    return r;
+  auto need = [&](bool f) {
+    return carved_bytes(carve_mtp, target, mtp->layer, B, W, mtp_kv->max_blocks_per_seq, f);
+  };
+  bool fine = false;
+  if (int r = check_attn_ws(workspace, workspace_bytes, need, fine)) return r;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   molt::Carver c(workspace, workspace_bytes);
-  MtpWs w = carve_mtp(c, target, mtp->layer, B, W, mtp_kv->max_blocks_per_seq);
+  MtpWs w = carve_mtp(c, target, mtp->layer, B, W, mtp_kv->max_blocks_per_seq, fine);
   const molt_model* L = mtp->layer;
   const int d = target->d_model, V = target->vocab, T = B * W;
   const molt_dtype dt = target->dtype;

@@ -814,11 +814,14 @@ __global__ __launch_bounds__(kF32AttnWaves * kWave) void attn_f32_kernel(
 // empty (a few sequences of short contexts), at least 8: there a split's time is its chain of steps
 // (us with the merge, splits of 32 / 8 blocks: one sequence at context 1500 20 / 15, 4 at 300..600
 // 19.6 / 15.7; with 120 and 240 workgroups, 30 at 300..600 21.5 / 25.4 and 60 at 100..300 23 / 33).
-void split_plan(long units, int max_blocks, int& splits, int& bps) {
+// The splits of 8 blocks can need more workspace than a larger batch or longer tables do, so they are
+// taken only where the caller's workspace holds them (`fine`): one that was sized for other arguments
+// and holds the 32-block splits serves too.
+void split_plan(long units, int max_blocks, bool fine, int& splits, int& bps) {
   const long pairs = units;
   int s = int((512 + pairs - 1) / pairs);
   int cap = (max_blocks + 31) / 32;
-  if (pairs * cap <= 64) cap = (max_blocks + 7) / 8;
+  if (fine && pairs * cap <= 64) cap = (max_blocks + 7) / 8;
   if (s > cap) s = cap;
   if (s < 1) s = 1;
   if (s < (max_blocks + kMaxSplitBlocks - 1) / kMaxSplitBlocks)
@@ -850,10 +853,10 @@ static void qtile_plan(int G, int kp1, int& qtiles, int& tq) {
   qtiles = (kp1 + tq - 1) / tq;
 }
 
-size_t attention_ws_bytes(int B, int k, int Hq, int Hkv, int D, int max_blocks) {
+size_t attention_ws_bytes(int B, int k, int Hq, int Hkv, int D, int max_blocks, bool fine) {
   int S, bps, qtiles, tq;
   qtile_plan(Hq / Hkv, k + 1, qtiles, tq);
-  split_plan(long(B) * Hkv * qtiles, max_blocks, S, bps);
+  split_plan(long(B) * Hkv * qtiles, max_blocks, fine, S, bps);
   if (S <= 1) return 0;
   const long rows = long(B) * (k + 1) * Hq;   // = B * Hkv * R
   Carver c(nullptr, 0);
@@ -865,7 +868,7 @@ size_t attention_ws_bytes(int B, int k, int Hq, int Hkv, int D, int max_blocks) 
 hipError_t launch_paged_attention(const void* q, const void* kc, const void* vc, const int32_t* bt,
                                   const int32_t* ctx, int B, int k, int Hq, int Hkv, int D,
                                   int max_blocks, molt_dtype dt, void* out, bool out_tiled,
-                                  void* ws, hipStream_t s) {
+                                  void* ws, bool fine, hipStream_t s) {
   AttnParams p{};
   p.out_tiled = out_tiled;
   p.q = static_cast<const uint16_t*>(q);
@@ -887,7 +890,7 @@ hipError_t launch_paged_attention(const void* q, const void* kc, const void* vc,
     return hipGetLastError();
   }
   qtile_plan(Hq / Hkv, k + 1, p.qtiles, p.tq);
-  split_plan(long(B) * Hkv * p.qtiles, max_blocks, p.splits, p.blocks_per_split);
+  split_plan(long(B) * Hkv * p.qtiles, max_blocks, fine, p.splits, p.blocks_per_split);
   if (p.splits > 1) {
     const long rows = long(B) * (k + 1) * Hq;
     Carver c(ws, 0);

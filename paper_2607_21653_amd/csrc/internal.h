@@ -151,11 +151,12 @@ hipError_t launch_moe_down(const void* a, const float* a_scale, const int32_t* p
 // multiple of 32 with zeros
 hipError_t launch_pack_tiled(const void* src, void* dst, long rows, long row_bytes, hipStream_t s);
 // ------------------------------------------------------------- attention
-size_t attention_ws_bytes(int B, int k, int Hq, int Hkv, int D, int max_blocks);
+// Workspace of the split key range; fine: with the finer splits of few sequences (launch with the same)
+size_t attention_ws_bytes(int B, int k, int Hq, int Hkv, int D, int max_blocks, bool fine);
 // out [T, Hq*D] row-major, or tiled (rows padded to 32 by the caller) with out_tiled
 hipError_t launch_paged_attention(const void* q, const void* kc, const void* vc, const int32_t* bt,
                                   const int32_t* ctx, int B, int k, int Hq, int Hkv, int D,
                                   int max_blocks, molt_dtype dt, void* out, bool out_tiled,
-                                  void* ws, hipStream_t s);
+                                  void* ws, bool fine, hipStream_t s);
 
 }  // namespace molt
