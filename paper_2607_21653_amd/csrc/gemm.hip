@@ -108,7 +108,9 @@ MOLT_DEV StreamTile stream_geometry(const GemmParams& p, int id, int nk, int wav
     wrow = long(g.expert) * 2 * p.N + (wave < 2 ? g.n0 + 32 * wave : p.N + g.n0 + 32 * (wave - 2));
   } else {
     g.n0 = nt * kBN;
-    wrow = long(g.expert) * p.N + g.n0 + 32 * wave;
+    // N is a multiple of 64: in a half column tile the last two wavefronts repeat the last rows
+    // (their columns are not stored)
+    wrow = long(g.expert) * p.N + min(g.n0 + 32 * wave, p.N - 32);
   }
   g.b = static_cast<const uint8_t*>(p.B) + wrow * RB;
   g.a = static_cast<const uint8_t*>(p.A) + long(g.row0) * RB;
@@ -418,7 +420,7 @@ void stream_gemm_kernel(GemmParams p) {
           const int u = int(threadIdx.x) + kThreads * j;
           const int r = u / (kEpCols / 4), c4 = (u % (kEpCols / 4)) * 4;
           const int grow = g.row0 + r;
-          if (grow >= g.row1) return;
+          if (grow >= g.row1 || g.n0 + c0 + c4 >= p.N) return;
           float4 v = *reinterpret_cast<const float4*>(dep + r * kEpCols + c4);
           const int c = g.n0 + c0 + c4;
           if (FP8) {
@@ -1599,7 +1601,7 @@ hipError_t launch_moe_down(const void* a, const float* a_scale, const int32_t* p
     p.n_ntiles = (d + kBigBN - 1) / kBigBN;
     return run_grouped_big<kDown, false>(p, s);
   }
-  p.n_ntiles = d / kBN;
+  p.n_ntiles = (d + kBN - 1) / kBN;
   if (wdt == MOLT_FP8_E4M3) return run_stream<true, kDown>(p, plan.tile_m, s);
   return run_stream<false, kDown>(p, plan.tile_m, s);
 }
