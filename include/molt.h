@@ -207,7 +207,8 @@ int molt_pack_weights(const void* src, void* dst, long long rows, long long row_
  *   block_tables  [B, max_blocks_per_seq] i32;  context_lens [B] i32
  *   out           [T, Hq*D]   dtype
  * Supported: dtype F32 or BF16, D in {64, 128}, Hq % Hkv == 0, Hq/Hkv*(1+k) <= 128.
- * context_lens[b] + k + 1 <= 16 * max_blocks_per_seq is the caller's duty.
+ * context_lens[b] + k + 1 <= 16 * max_blocks_per_seq is the caller's duty. Slots past a
+ * sequence's last position may hold anything, infinities and NaN too.
  * Workspace: partial results of splits of the key range. For few sequences of short tables the
  * size includes finer splits, which a larger batch or longer tables do not need; a smaller
  * workspace that holds the splits of at least 32 blocks each is accepted too and used with

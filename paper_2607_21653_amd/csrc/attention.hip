@@ -81,6 +81,19 @@ MOLT_DEV int kswz(int key, int blk) {
 }
 MOLT_DEV int vswz(int dim) { return ((dim >> 2) ^ (dim >> 3)) & 1; }
 
+// Mask of 8 consecutive keys of V from key `first`: ones for those before `end`, the last key that the
+// query tile sees. The rest are slots of its last block that nothing may have been written to (or the
+// repeated block of an odd pair). Their probabilities are 0, but 0 times an infinity or NaN is not, so
+// the last pair's V is cleared there in LDS, by the threads that copied it, before the barrier that
+// hands it over (long-context layer, us: 520 without and with it; masked in the staging registers, whose
+// loads the branch then waits for, 554; at the MFMAs, where the mask costs a wavefront per SIMD, 598).
+MOLT_DEV int32x4_t v_mask(int first, int end) {
+  int32x4_t m;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) m[i] = (first + 2 * i < end ? 0xffff : 0) | (first + 2 * i + 1 < end ? int(0xffff0000u) : 0);
+  return m;
+}
+
 // Row r of a query tile (position j0 + r / G, query head h G + r % G): its output, or this split's
 // partials. o(dt): the lane's elements of O^T tile dt, dims 16 dt + 4 g4 + e; lt the row's sum.
 template <int D, typename O>
@@ -124,7 +137,7 @@ __global__ __launch_bounds__(512, 2) void attn_lds_kernel(AttnParams p) {
   constexpr int PAIR = 4 * KB;          // K0, K1, V0, V1
   constexpr int CPT = PAIR / 16 / kThreads;   // 16-byte chunks per thread per pair
   static_assert(CPT >= 1 && CPT * 16 * kThreads == PAIR, "chunks per thread");
-  // steps (KS pairs each) loaded ahead into registers: with one, 119 registers, so that two
+  // steps (KS pairs each) loaded ahead into registers: with one, 120 registers, so that two
   // workgroups fit per CU (two steps ahead at one per CU took the same time)
   constexpr int kDepth = 1;
   __shared__ __attribute__((aligned(16))) uint8_t lds[2 * KS][PAIR];
@@ -247,6 +260,21 @@ __global__ __launch_bounds__(512, 2) void attn_lds_kernel(AttnParams p) {
 #pragma unroll
       for (int u = 0; u < CPT; ++u) *reinterpret_cast<int32x4_t*>(lds[KS * hf + g] + dst_off[u]) = src[g][u];
   };
+  // the last pair (of step clear_si, if it needs it), once stored: each thread its own chunks of V
+  const int nsteps = (npairs + KS - 1) / KS;
+  const int vend = min(nkeys, blk1 * 16);
+  const int clear_si = (blk0 + 2 * npairs) * 16 > vend ? nsteps - 1 : -1;
+  auto clear_v = [&](int hf) __attribute__((always_inline)) {
+    const int pb = blk0 + 2 * (npairs - 1);
+#pragma unroll
+    for (int u = 0; u < CPT; ++u) {
+      const int c = threadIdx.x + kThreads * u, q = c / (KB / 16), ch = c % (KB / 16);
+      if (q < 2) continue;
+      const int dim = ch / 2, vc = ch % 2;
+      int32x4_t* v = reinterpret_cast<int32x4_t*>(lds[KS * hf + (npairs - 1) % KS] + q * KB + dim * 32 + ((vc ^ vswz(dim)) * 16));
+      *v &= v_mask((pb + (q & 1)) * 16 + 8 * vc, vend);
+    }
+  };
 
   // K fragment: block j = l16 / 8, key 8 ((l16 / 4) % 2) + 4 t + l16 % 4 (the swizzle is the
   // same for t = 0 and 1, so t only adds 4 rows), chunk 4 s + g4 (dims 32 s + 8 g4).
@@ -344,13 +372,13 @@ __global__ __launch_bounds__(512, 2) void attn_lds_kernel(AttnParams p) {
   // other half (last read before the previous barrier) and refills its slot with step
   // si + 1 + kDepth, so the new loads are in flight during the compute; then each key group
   // computes its pair of step si. Loads past the last pair re-read it.
-  const int nsteps = (npairs + KS - 1) / KS;
   auto step = [&](int hf, int si) __attribute__((always_inline)) {
     if (KS * si + kg < npairs) compute(KS * hf + kg, KS * si + kg);
   };
   if (nsteps > 0) {
     gload(st[0], 0);
     sstore(st[0], 0);
+    if (clear_si == 0) clear_v(0);
 #pragma unroll
     for (int u = 1; u <= kDepth; ++u) gload(st[u % kDepth], u);
     lds_barrier();
@@ -363,6 +391,7 @@ __global__ __launch_bounds__(512, 2) void attn_lds_kernel(AttnParams p) {
         sstore(st[(u + 1) % kDepth], 1 - (par ^ (u & 1)));
         gload(st[(u + 1) % kDepth], si + u + 1 + kDepth);
         step(par ^ (u & 1), si + u);
+        if (si + u + 1 == clear_si) clear_v(1 - (par ^ (u & 1)));
         lds_barrier();
       }
     }
@@ -372,6 +401,7 @@ __global__ __launch_bounds__(512, 2) void attn_lds_kernel(AttnParams p) {
       if (si + u < nsteps) {
         sstore(st[(u + 1) % kDepth], 1 - (par ^ (u & 1)));
         step(par ^ (u & 1), si + u);
+        if (si + u + 1 == clear_si) clear_v(1 - (par ^ (u & 1)));
         lds_barrier();
       }
     }
@@ -519,12 +549,24 @@ MOLT_DEV void attn_rows_walk(const AttnParams& p, uint8_t* ring, const RowTile& 
   }
   if (npairs > 0) {
     int id = block_id(0);
+    const int vend = min(lim_lo + Rt / G, blk1 * 16);
 #pragma unroll
     for (int u = 0; u < kRowStages - 1; ++u) {
       issue(u, id);
       id = block_id(u + 1);
     }
     for (int pi = 0; pi < npairs; ++pi) {
+      if ((blk0 + 2 * pi + 2) * 16 > vend && wave >= 2) {
+        // the last pair: a wavefront that copies V clears the chunks it copied (see v_mask)
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NI) : "memory");
+        uint8_t* own = ring + (pi % kRowStages) * PAIR + wave * KB + lane * 16;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+          const int dim = (i * kWave + lane) / 2, s = (lane % 2) ^ vswz(dim);
+          int32x4_t* ch = reinterpret_cast<int32x4_t*>(own + i * 1024);
+          *ch &= v_mask((blk0 + 2 * pi + (wave & 1)) * 16 + 8 * s, vend);
+        }
+      }
       // this wavefront's copies of pair pi are in (two later pairs may be in flight) and its
       // reads of pair pi - 1 have returned: after the barrier pair pi is complete for everyone
       // and the stage of pair pi - 1 takes pair pi + 3
