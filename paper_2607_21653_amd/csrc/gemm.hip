@@ -10,6 +10,10 @@
 // the permutation kernel, so the host never reads expert counts.
 //
 // The f32 model takes an f32 MFMA kernel over the same layouts.
+#include <math.h>
+
+#include <algorithm>
+
 #include "device_common.h"
 #include "internal.h"
 
@@ -1433,20 +1437,53 @@ __global__ __launch_bounds__(kF32Waves * kWave) void f32_gemm_kernel(GemmParams 
 
 }  // namespace
 
+// Row tiles of height h of one expert, on average: avg rows with the spread of T tokens that choose K of
+// E experts alike (the share of experts past each multiple of h, linear over +-1.2 standard deviations).
+static double expert_tiles(double avg, double share, int h) {
+  const double width = 2.4 * sqrt(avg * std::max(0.0, 1.0 - share));
+  if (width == 0.0) return ceil(avg / h);
+  const long whole = std::max(0L, long((avg - 0.5 * width) / h));       // passed by every expert
+  double n = 1.0 + double(whole);
+  for (long j = whole + 1;; ++j) {
+    const double p = (avg - double(j * h)) / width + 0.5;
+    if (p <= 0.0) return n;
+    n += std::min(p, 1.0);
+  }
+}
+
 // Grouped expert GEMMs. Weight-streaming kernel: row tiles large enough that an expert of average
 // load fits one (its weights are then streamed once), as small as that allows. From 120 rows per
-// expert on average, where many experts need a second 128-row tile, the big-tile kernel takes bf16
+// expert on average, where many experts need a second 128-row tile, the big-tile kernel may take bf16
 // experts (us gate_up + down at d 2048, F 768, 128 experts top-8, streaming / big-tile: T = 4000
 // 379 + 224 / 275 + 173, 2300 324 + 177 / 191 + 135, 1800 186 + 108 / 175 + 126, 1500 169 + 100 /
-// 167 + 122). fp8 experts stay: their weights are half the bytes, and a version of the big-tile
-// kernel in fp8 measured 125 + 95 against 131 + 93 at 2304 rows with skewed load.
+// 167 + 122). Its tiles are four times as large, so with few of them they leave the chip idle (E 8,
+// top-2, 256 rows each, same d and F: 48 / 71). Either way a launch takes the longer of its rounds of
+// tiles, each alone on its place of the chip (512 places / 256), and of all tiles' 128-byte K slices at
+// the rate of a full chip; the constants (us) are fitted to both launches at 593 shapes (E 1..128, 120..4096
+// rows, five d x F from 512 x 256 to 2048 x 6144): the choice costs 0.7% over the better kernel on
+// average (big-tile from 120 rows on, without regard to the tiles: 16%). fp8 experts stay: their weights are
+// half the bytes, and a version of the big-tile kernel in fp8 measured 125 + 95 against 131 + 93 at
+// 2304 rows with skewed load.
 MoePlan moe_plan(molt_dtype wdt, int T, int K, int E, int d, int F) {
   if (wdt == MOLT_F32) return {32, false};
   const long avg = (long(T) * K + E - 1) / E;
   const long lim = 1L << 31;           // 32-bit buffer offsets into each operand
-  if (wdt == MOLT_BF16 && avg >= 120 && 2L * T * d < lim && 4L * T * K * d < lim && 4L * F * d < lim)
-    return {256, true};
-  return {avg <= 24 ? 32 : avg <= 56 ? 64 : 128, false};
+  const MoePlan stream{avg <= 24 ? 32 : avg <= 56 ? 64 : 128, false};
+  if (wdt != MOLT_BF16 || avg < 120 || 2L * T * d >= lim || 4L * T * K * d >= lim || 4L * F * d >= lim)
+    return stream;
+  const double share = double(K) / E;
+  const double ms = E * expert_tiles(double(avg), share, 128), mb = E * expert_tiles(double(avg), share, 256);
+  const double fill = 0.6 + 0.4 * std::min(1.0, double(avg) * E / mb / 256.0);   // a low tile's steps are shorter
+  auto stream_us = [&](int nk, int nt) {
+    return std::max(ceil(ms * nt / 512.0) * (8.0 + 0.5 * nk), ms * nt * (nk + 1.0) * 0.0038);
+  };
+  auto big_us = [&](int nk, int nt) {
+    return std::max(ceil(mb * nt / 256.0) * (11.5 + 1.15 * fill * nk), mb * nt * (nk + 4.0) * 0.0084);
+  };
+  const int nkg = d / 64, nkd = F / 64;                // K slices of gate_up and of down
+  const double ts = stream_us(nkg, F / 64) + stream_us(nkd, (d + 127) / 128);
+  const double tb = big_us(nkg, (F + 127) / 128) + big_us(nkd, (d + 255) / 256);
+  return tb < ts ? MoePlan{256, true} : stream;
 }
 
 // Plan of a dense bf16 GEMM: big tiles of 32 ab rows x 256 columns (ab > 0), or the LDS-tiled

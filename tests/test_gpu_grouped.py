@@ -1,6 +1,6 @@
-"""The grouped big-tile expert GEMMs (bf16, experts of 120 rows on average and more) at the edges
-of their tiles: every split of an expert's rows into 32-row blocks, halves and tiles (0, 1, 33 ..
-513 rows: halves of different heights, an empty second half, several tiles), fewer K slices than
+"""Expert GEMMs of bf16 experts with 120 rows on average and more, few of them (too few tiles for the
+big-tile kernel: they run on 128-row weight-streaming tiles), at the edges of the tiles: every split
+of an expert's rows into 32-row blocks and tiles (0, 1, 33 .. 513 rows), fewer K slices than
 the pipeline is deep and counts that no depth divides, last column tiles that are part empty.
 The reference takes the SwiGLU product in bf16 as the library stores it; a rounding of it that
 goes the other way moves an output by 2^-8 of one of its F terms."""
