@@ -27,6 +27,8 @@
 // rescaled lazily, only when a row maximum grows by more than 8 (in log2 units) over the
 // reference it was accumulated with. Splits are merged by a log-sum-exp pass (a single
 // split writes the output directly). Deterministic.
+#include <limits.h>
+
 #include "device_common.h"
 #include "internal.h"
 
@@ -86,7 +88,11 @@ MOLT_DEV int vswz(int dim) { return ((dim >> 2) ^ (dim >> 3)) & 1; }
 // repeated block of an odd pair). Their probabilities are 0, but 0 times an infinity or NaN is not, so
 // the last pair's V is cleared there in LDS, by the threads that copied it, before the barrier that
 // hands it over (long-context layer, us: 520 without and with it; masked in the staging registers, whose
-// loads the branch then waits for, 554; at the MFMAs, where the mask costs a wavefront per SIMD, 598).
+// loads the branch then waits for, 554; at the MFMAs, where the mask costs a wavefront per SIMD, 598). The
+// lane is opaque to the compiler there, so that the addresses and masks are formed by the last pair alone:
+// hoisted to the kernel's start they cost short calls more than the clearing (16 query heads over 2 of
+// dimension 64, 9 positions, 64 sequences at context 1000: 20.5 without, 21.7 hoisted, 20.8 now; 8 heads of
+// dimension 128, 5 positions, 16 sequences at context 500: 15.5 / 16.4 / 15.7).
 MOLT_DEV int32x4_t v_mask(int first, int end) {
   int32x4_t m;
 #pragma unroll
@@ -266,9 +272,11 @@ __global__ __launch_bounds__(512, 2) void attn_lds_kernel(AttnParams p) {
   const int clear_si = (blk0 + 2 * npairs) * 16 > vend ? nsteps - 1 : -1;
   auto clear_v = [&](int hf) __attribute__((always_inline)) {
     const int pb = blk0 + 2 * (npairs - 1);
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));         // see v_mask
 #pragma unroll
     for (int u = 0; u < CPT; ++u) {
-      const int c = threadIdx.x + kThreads * u, q = c / (KB / 16), ch = c % (KB / 16);
+      const int c = tid + kThreads * u, q = c / (KB / 16), ch = c % (KB / 16);
       if (q < 2) continue;
       const int dim = ch / 2, vc = ch % 2;
       int32x4_t* v = reinterpret_cast<int32x4_t*>(lds[KS * hf + (npairs - 1) % KS] + q * KB + dim * 32 + ((vc ^ vswz(dim)) * 16));
@@ -550,19 +558,23 @@ MOLT_DEV void attn_rows_walk(const AttnParams& p, uint8_t* ring, const RowTile& 
   if (npairs > 0) {
     int id = block_id(0);
     const int vend = min(lim_lo + Rt / G, blk1 * 16);
+    // the split ends in the sequence's last block, and that has such slots (a window's earlier tiles end in
+    // blocks that the window has filled)
+    const int clear_blk = blk1 * 16 > ctx + kp1 ? blk1 : INT_MAX;
 #pragma unroll
     for (int u = 0; u < kRowStages - 1; ++u) {
       issue(u, id);
       id = block_id(u + 1);
     }
     for (int pi = 0; pi < npairs; ++pi) {
-      if ((blk0 + 2 * pi + 2) * 16 > vend && wave >= 2) {
-        // the last pair: a wavefront that copies V clears the chunks it copied (see v_mask)
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NI) : "memory");
-        uint8_t* own = ring + (pi % kRowStages) * PAIR + wave * KB + lane * 16;
+      if (blk0 + 2 * pi + 2 >= clear_blk && wave >= 2) {
+        // the last pair: a wavefront that copies V clears the chunks it copied
+        int ln = lane;                    // opaque, see v_mask
+        asm volatile("s_waitcnt vmcnt(%1)" : "+v"(ln) : "n"(2 * NI) : "memory");
+        uint8_t* own = ring + (pi % kRowStages) * PAIR + wave * KB + ln * 16;
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
-          const int dim = (i * kWave + lane) / 2, s = (lane % 2) ^ vswz(dim);
+          const int dim = (i * kWave + ln) / 2, s = (ln % 2) ^ vswz(dim);
           int32x4_t* ch = reinterpret_cast<int32x4_t*>(own + i * 1024);
           *ch &= v_mask((blk0 + 2 * pi + (wave & 1)) * 16 + 8 * s, vend);
         }
