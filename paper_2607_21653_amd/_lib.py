@@ -163,11 +163,12 @@ def _workspace(nbytes, device, ws=None):
 def _call(name, call, nbytes, device, ws):
     """call(workspace address, its bytes) with the caller's workspace, also a smaller one where the
     library takes it (coarser attention splits), else with one of nbytes."""
-    if ws is not None and ws.numel() < nbytes:
-        status = call(_ptr(ws), ws.numel())
-        if status != MOLT_ERR_WORKSPACE:
+    have = 0 if ws is None else ws.numel()
+    if have:
+        status = call(_ptr(ws), have)
+        if have >= nbytes or status != MOLT_ERR_WORKSPACE:
             return _check(status, name)
-    t, nb = _workspace(nbytes, device, ws)
+    t, nb = _workspace(nbytes, device)
     _check(call(_ptr(t), nb), name)
 
 
