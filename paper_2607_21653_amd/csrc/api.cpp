@@ -348,6 +348,12 @@ hipError_t run_moe(const MoeWs& m, const void* x, const void* x_rows, const floa
   // gate_up's rows: the tiled x for f32, else row-major: x itself, or its fp8 codes, which the
   // caller has already (x_rows with xs) or which are made here from x
   const void* src = wdt == MOLT_F32 ? x : x_rows;
+  if (m.plan.big && reinterpret_cast<uintptr_t>(src) % 16 != 0) {
+    // the big-tile kernel's LDS-DMA takes aligned rows: a copy in o, which nothing holds before down
+    if ((e = hipMemcpyAsync(m.o, src, size_t(T) * d * dt_size(wdt), hipMemcpyDeviceToDevice, s)) != hipSuccess)
+      return e;
+    src = m.o;
+  }
   if (fp8 && xs == nullptr) {
     if ((e = molt::launch_quant_rows(static_cast<const uint16_t*>(x_rows), T, d, m.xq, m.xs, s)) !=
         hipSuccess)

@@ -466,6 +466,9 @@ __global__ __launch_bounds__(512, 2) void attn_lds_kernel(AttnParams p) {
 constexpr int kRawRsrcWord3 = 0x00020000;   // raw byte-addressed buffer
 constexpr int kRowStages = 4;
 constexpr int kRowWaves = 4;
+// LDS-DMA of 16 bytes a lane is used at aligned addresses only. Caches that do not start at a multiple of 16
+// bytes are copied through registers (DMA = false), each block where its LDS-DMA would be issued.
+typedef int32x4_t Unaligned16 __attribute__((aligned(2)));
 
 // What a workgroup of attn_rows_kernel works on (all uniform).
 struct RowTile {
@@ -474,7 +477,7 @@ struct RowTile {
 
 // The walk of a wavefront with RT 16-row tiles from tile t0 (0: only its copies) over the
 // split's pairs, and its rows' outputs.
-template <int D, bool NT, int RT>
+template <int D, bool NT, bool DMA, int RT>
 MOLT_DEV void attn_rows_walk(const AttnParams& p, uint8_t* ring, const RowTile& w, int t0, int wave) {
   constexpr int DS = D / 32;            // 32-dim k-steps for S
   constexpr int DT = D / 16;            // 16-dim tiles of O^T
@@ -511,6 +514,14 @@ MOLT_DEV void attn_rows_walk(const AttnParams& p, uint8_t* ring, const RowTile& 
     const uint16_t* src = cache + (long(id) * p.Hkv + h) * (16 * D);
     const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(src), 0, pi < npairs ? KB : 0, kRawRsrcWord3);
     uint8_t* dst = ring + (pi % kRowStages) * PAIR + wave * KB;
+    if constexpr (!DMA) {
+      if (pi < npairs)
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+          *reinterpret_cast<int32x4_t*>(dst + i * 1024 + lane * 16) =
+              *reinterpret_cast<const Unaligned16*>(reinterpret_cast<const uint8_t*>(src) + voff[i]);
+      return;
+    }
 #pragma unroll
     for (int i = 0; i < NI; ++i)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)(dst + i * 1024), 16,
@@ -677,7 +688,7 @@ MOLT_DEV void attn_rows_walk(const AttnParams& p, uint8_t* ring, const RowTile& 
   }
 }
 
-template <int D, bool NT>
+template <int D, bool NT, bool DMA>
 __global__ __launch_bounds__(kRowWaves * kWave, 2) void attn_rows_kernel(AttnParams p) {
   __shared__ __attribute__((aligned(16))) uint8_t ring[kRowStages * 4 * 16 * D * 2];   // the only LDS object
 
@@ -706,9 +717,9 @@ __global__ __launch_bounds__(kRowWaves * kWave, 2) void attn_rows_kernel(AttnPar
   const int t0 = wave * ntile / kRowWaves, t1 = (wave + 1) * ntile / kRowWaves;
 
   const RowTile w{b, h, bh, split, ctx, j0, Rt, r0, blk0, blk1, npairs};
-  if (t1 - t0 == 2) attn_rows_walk<D, NT, 2>(p, ring, w, t0, wave);
-  else if (t1 - t0 == 1) attn_rows_walk<D, NT, 1>(p, ring, w, t0, wave);
-  else attn_rows_walk<D, NT, 0>(p, ring, w, t0, wave);
+  if (t1 - t0 == 2) attn_rows_walk<D, NT, DMA, 2>(p, ring, w, t0, wave);
+  else if (t1 - t0 == 1) attn_rows_walk<D, NT, DMA, 1>(p, ring, w, t0, wave);
+  else attn_rows_walk<D, NT, DMA, 0>(p, ring, w, t0, wave);
 }
 
 // log-sum-exp merge over splits: one workgroup per (b, h, group of 1024 / D rows), each
@@ -891,8 +902,10 @@ hipError_t launch_d(const AttnParams& p, int B, int R, hipStream_t s) {
   const long grid = long(B) * p.Hkv * p.qtiles * p.splits;
   // two key groups when a query tile's row tiles fit half the wavefronts
   if ((Rt + 15) / 16 <= 4) attn_lds_kernel<D><<<grid, 512, 0, s>>>(p);
-  else if (p.qtiles == 1) attn_rows_kernel<D, true><<<grid, kRowWaves * kWave, 0, s>>>(p);
-  else attn_rows_kernel<D, false><<<grid, kRowWaves * kWave, 0, s>>>(p);
+  else if ((reinterpret_cast<uintptr_t>(p.kc) | reinterpret_cast<uintptr_t>(p.vc)) % 16 != 0)
+    attn_rows_kernel<D, false, false><<<grid, kRowWaves * kWave, 0, s>>>(p);
+  else if (p.qtiles == 1) attn_rows_kernel<D, true, true><<<grid, kRowWaves * kWave, 0, s>>>(p);
+  else attn_rows_kernel<D, false, true><<<grid, kRowWaves * kWave, 0, s>>>(p);
   if (p.splits > 1) attn_merge_kernel<D><<<B * p.Hkv * ((R + 1024 / D - 1) / (1024 / D)), 256, 0, s>>>(p);
   return hipGetLastError();
 }

@@ -137,7 +137,8 @@ hipError_t launch_qkv_rope(const void* A, const void* Bw, int M, int K_in, int H
 struct MoePlan { int tile_m; bool big; };
 MoePlan moe_plan(molt_dtype wdt, int T, int K, int E, int d, int F);
 // Grouped expert GEMMs over the tile table built by launch_route. gate_up reads each padded row's
-// token row through pperm: a = the token rows in the expert dtype, row-major [T, K] (f32: tiled);
+// token row through pperm: a = the token rows in the expert dtype, row-major [T, K] (f32: tiled; big:
+// 16-byte aligned);
 // weights, h and down's a in the tiled layout, rows of h in padded order; down writes o[pair].
 hipError_t launch_moe_gate_up(const void* a, const float* a_scale, const int32_t* pperm,
                               int K_top, const void* w_gu, const float* s_gu, int T, int d, int F, molt_dtype wdt, const int32_t* tiles,
