@@ -1488,12 +1488,15 @@ MoePlan moe_plan(molt_dtype wdt, int T, int K, int E, int d, int F) {
 
 // Plan of a dense bf16 GEMM: big tiles of 32 ab rows x 256 columns (ab > 0), or the LDS-tiled
 // kernel with bm x 128 tiles and split-K. LDS-tiled: 128-row tiles when there are plenty of
-// them, else 64; then the K range is halved while the grid is under one workgroup per CU, each
-// split keeps >= 4 slices and the partial sums fit `part_elems` floats.
+// them, else 64 (and with the RoPE epilogue, whose rows take the big tiles long before); then the K
+// range is halved while the grid is under one workgroup per CU, each split keeps >= 4 slices and the
+// partial sums fit `part_elems` floats. Of 128-row tiles that leaves outputs of up to 128 columns and
+// more than 65k rows (with the packing, us, 64 / 128 rows: 65500 x 128 x 2048 325 / 304, 66000 x 64 x
+// 2048 318 / 315) and operands past 32-bit offsets.
 // Between them the busiest CU decides: tiles per CU (rounded up) x the time of one tile, which
 // was measured per 32 slices with the chip full (us): LDS-tiled 64 rows 11.5, 128 rows 20.5;
-// big tiles of 64 rows 18, 96 rows 24, 128 rows 30, 160 rows 40; with the RoPE epilogue 13, 24
-// and 20.5, 28.5, 33, 54 (160 rows leave one workgroup a CU, with nothing to hide the epilogue
+// big tiles of 64 rows 18, 96 rows 24, 128 rows 30, 160 rows 40; with the RoPE epilogue 64 rows 13
+// and big tiles 20.5, 28.5, 33 (160 rows, 54, leave one workgroup a CU, with nothing to hide the epilogue
 // behind: not used). The kernels both ways (us, LDS-tiled / big): 4000 x 5120 x 2048 135 / 87
 // (160 rows), 4000 x 2048 x 4096 85 / 65 (128 rows), 2304 x 5120 x 2048 62 / 47 and 2304 x 2048
 // x 4096 64 / 42 (96 rows), 640 x 5120 x 2048 25 / 21 (64 rows); 1024 x 2048 x 4096 26 / 32 and
@@ -1503,15 +1506,15 @@ GemmPlan gemm_plan(int M, int N, int K, long part_elems, bool rope) {
   constexpr long kCus = 256;
   GemmPlan g{128, 1, 0};
   const long nt = (N + kBN - 1) / kBN;
-  if ((M + 127) / 128 * nt < 512) g.bm = 64;
+  if (rope || (M + 127) / 128 * nt < 512) g.bm = 64;
   const long wg = (M + g.bm - 1) / g.bm * nt;
   const int nk = int(2L * K / kRowBytes);
   long splits = 1;                       // without the limit of part_elems
   while (!rope && wg * splits < 256 && nk / (2 * splits) >= 4) splits *= 2;
   if (long(M + 31) * 2 * K < (1L << 31) && long(kBigBN) * 2 * K < (1L << 31)) {   // 32-bit buffer offsets
-    constexpr double kTile[2][6] = {{0, 0, 18.0, 24.0, 30.0, 40.0}, {0, 0, 20.5, 28.5, 33.0, 54.0}};
-    constexpr double kLdsTile[2][2] = {{11.5, 20.5}, {13.0, 24.0}};
-    double best = double((wg * splits + kCus - 1) / kCus) * kLdsTile[rope][g.bm / 128] / double(splits);
+    constexpr double kTile[2][6] = {{0, 0, 18.0, 24.0, 30.0, 40.0}, {0, 0, 20.5, 28.5, 33.0}};
+    const double lds_tile = rope ? 13.0 : g.bm == 64 ? 11.5 : 20.5;
+    double best = double((wg * splits + kCus - 1) / kCus) * lds_tile / double(splits);
     for (int ab = 2; ab <= (rope ? 4 : 5); ++ab) {
       const long tiles = long((M + 32 * ab - 1) / (32 * ab)) * ((N + kBigBN - 1) / kBigBN);
       const double t = double((tiles + kCus - 1) / kCus) * kTile[rope][ab];
@@ -1581,11 +1584,10 @@ hipError_t launch_qkv_rope(const void* A, const void* Bw, int M, int K_in, int H
   }
   const GemmPlan g = gemm_plan(M, p.N, K_in, 0, true);   // no split: the epilogue needs whole sums
   if (g.ab > 0) return run_bigtile<kBigRope>(p, rk, g.ab, s);
-  p.n_mtiles = (M + g.bm - 1) / g.bm;
+  p.n_mtiles = (M + 63) / 64;
   p.n_ntiles = Hq + 2 * Hkv;
   const int grid = (p.n_mtiles * p.n_ntiles + 7) / 8 * 8;
-  if (g.bm == 64) lds_gemm_kernel<64, true, 4, 2><<<grid, 512, 0, s>>>(p, nullptr, 1, rk);
-  else lds_gemm_kernel<128, true, 2, 2><<<grid, kThreads, 0, s>>>(p, nullptr, 1, rk);
+  lds_gemm_kernel<64, true, 4, 2><<<grid, 512, 0, s>>>(p, nullptr, 1, rk);
   return hipGetLastError();
 }
 
