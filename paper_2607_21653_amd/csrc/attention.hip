@@ -913,8 +913,7 @@ hipError_t launch_d(const AttnParams& p, int B, int R, hipStream_t s) {
 }  // namespace
 
 // Query tiles of (b, h): all G(1+k) rows in one tile when they fit in 128 (every key and
-// value read once), else tiles of floor(128 / G) positions (at least one), each read by an
-// 8-wavefront workgroup.
+// value read once), else tiles of floor(128 / G) positions (at least one).
 static void qtile_plan(int G, int kp1, int& qtiles, int& tq) {
   tq = G * kp1 <= 128 ? kp1 : (G <= 128 ? 128 / G : 1);
   qtiles = (kp1 + tq - 1) / tq;

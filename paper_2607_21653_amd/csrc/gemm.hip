@@ -4,12 +4,14 @@
 // per-channel scales (v_mfma_f32_32x32x64_f8f6f4), f32 accumulation.
 //
 // Every operand is in the tiled layout of device_common.h (weights packed once at load;
-// activations written tiled by their producers, rows padded to a multiple of 32). One
-// kernel template streams the weights per wavefront (see below). Grouped launches run over
-// a device-side tile table (expert, first row, end row) in padded expert order built by
-// the permutation kernel, so the host never reads expert counts.
-//
-// The f32 model takes an f32 MFMA kernel over the same layouts.
+// activations written tiled by their producers, rows padded to a multiple of 32; the token
+// rows of gate_up row-major). Kernels, in the order of this file: weight streaming
+// (stream_gemm_kernel: grouped, and few rows by many columns), LDS-tiled (lds_gemm_kernel:
+// dense), few rows (qkv_few_kernel), big tiles (bigtile_gemm_kernel: dense;
+// grouped_bigtile_kernel: grouped) and f32 (f32_gemm_kernel: everything of the f32 model);
+// gemm_plan and moe_plan choose. Grouped launches run over a device-side tile table (expert,
+// first row, end row) in padded expert order built by the permutation kernel, so the host
+// never reads expert counts.
 #include <math.h>
 
 #include <algorithm>
@@ -500,9 +502,9 @@ hipError_t run_stream(GemmParams p, int tile_m, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------- LDS-tiled dense GEMM
-// Dense projections and the LM head have a few hundred rows: every weight tile feeds
+// Dense projections of a few hundred rows: every weight tile feeds
 // several row tiles and every activation tile many column tiles, so both operands are
-// shared through LDS. Workgroup = BM x 128 outputs, 4 wavefronts in a 2 x 2 grid. Per
+// shared through LDS. Workgroup = BM x 128 outputs, wavefronts in a 2 x WN grid. Per
 // 128-byte K slice the workgroup copies (BM/32 + 4) tiled 4 KB blocks (one 16-byte chunk
 // per thread per block: coalesced 4 KB loads from one page) into a double-buffered LDS
 // ring, loaded two slices ahead into registers; the tiled layout makes each wavefront's
