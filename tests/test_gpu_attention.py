@@ -2,10 +2,8 @@
 paged blocks with split-KV merge) against the oracle's float64 paged attention: bf16
 within 1e-2 max-abs (outputs are rounded to bf16), f32 within 1e-5; ragged contexts,
 one-key and empty-context edges, k = 0, 8 drafts (72 query rows, also ragged with splits),
-9 drafts with many splits and 11 (96 rows) on the 8-wavefront tiles, head dim 64, many
-splits; prefill
-windows longer than one 128-row query
-tile (64, 41, 101 and 256 positions: several tiles, a partial last tile, tiles with splits,
+9 drafts with many splits and 11 (96 rows) on tiles of more than 64 rows, head dim 64, many
+splits; prefill windows longer than one 128-row query tile (64, 41, 101 and 256 positions: several tiles, a partial last tile, tiles with splits,
 an empty cached context); shuffled and contiguous block tables give bit-identical
 outputs."""
 import numpy as np

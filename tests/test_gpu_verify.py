@@ -139,7 +139,7 @@ def test_bf16_decoder_layer(molt_lib, fp8):
 
 def test_fp8_decoder_layer_zipf(molt_lib):
     """fp8 experts, B = 64, k = 8 (576 tokens) under Zipf routing: the popular experts span
-    several 128-row tiles, their rows read through the permutation from the RMSNorm's
+    several 64-row tiles, their rows read through the permutation from the RMSNorm's
     row-major codes."""
     w = workloads.FP8_ZIPF.scaled(batch=64, k=8, ctx_lo=100, ctx_hi=600)
     cfg = oracle_cfg(w)
@@ -175,7 +175,7 @@ def test_fp8_decoder_layer_zipf(molt_lib):
 
 
 def test_bf16_decoder_layer_many_tokens(molt_lib):
-    """T = 320 tokens: the dense projections run 128-row tiles with a ragged 64-row tail."""
+    """T = 320 tokens: the dense projections run several 64-row tiles, O and the router with split-K."""
     w = workloads.LAYER_BF16.scaled(batch=64, k=4, ctx_lo=40, ctx_hi=300)
     cfg = oracle_cfg(w)
     seed = 12
